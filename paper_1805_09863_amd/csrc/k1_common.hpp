@@ -155,17 +155,18 @@ struct Epilogue {
   }
 
   // One BV x BH tile of logits in acc (MFMA 32x32 layout: lane holds row
-  // (hypothesis) col of each 32-block and 16 vocabulary entries).
+  // (hypothesis) col of each 32-block and 16 vocabulary entries).  The tile
+  // starts at word v0; its words below vlo belong to the tile before.
   __device__ __forceinline__ void tile(f32x16 (&acc)[WV][WH], SmemEpi<L>& ep, const K1Args& a, int h0, int v0,
-                                       bool first, const uint32_t (&tg)[WH], const float* bias) {
+                                       int vlo, bool first, const uint32_t (&tg)[WH], const float* bias) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wv = wave % NWV, wh = wave / NWV;
     const int half = lane >> 5, col = lane & 31;
     const int holder = wv * 2 + half;
     const int k = a.k;
 
-    // ---- bias (Algorithm 3 AddBias, fused) and masking of words >= V
-    const bool ragged = (v0 + L::BV > a.V);
+    // ---- bias (Algorithm 3 AddBias, fused) and masking of words >= V or < vlo
+    const bool ragged = v0 + L::BV > a.V || v0 < vlo;
 #pragma unroll
     for (int vb = 0; vb < WV; ++vb) {
       const int vl = (wv * WV + vb) * 32 + 4 * half;
@@ -186,7 +187,7 @@ struct Epilogue {
           const int v = v0 + vl + 8 * (r >> 2) + (r & 3);
 #pragma unroll
           for (int hb = 0; hb < WH; ++hb)
-            if (v >= a.V) acc[vb][hb][r] = -INFINITY;
+            if (v >= a.V || v < vlo) acc[vb][hb][r] = -INFINITY;
         }
       }
     }

@@ -1,6 +1,5 @@
 // K1, DMA variant: the fused output-layer projection for 16-byte aligned
-// operands, bf16 h and W with H % 128 == 0 and V % 8 == 0, or float32 with
-// H % 64 == 0 and V % 4 == 0.
+// bf16 operands with H % 128 == 0 and V % 8 == 0.
 //
 // Same work split and epilogue as the register-staged kernel; the difference
 // is how operands reach the matrix cores.  A ring of NS LDS stages (BK = 32
@@ -13,29 +12,19 @@
 //   * h rows are stored row-major, 64 bytes (BK = 32 states) per row, with
 //     the four 16-byte chunks XOR-swizzled by row; one DMA instruction reads
 //     16 rows x 64 contiguous bytes, and B-fragment reads stay conflict-free.
-// Float32 (the fp32 MFMA 32x32x2): a stage holds BK = 16 states, the same
-// bytes per row of h (so the same h layout and swizzle) and 16 rows of W
-// stored as they arrive (a wave's A-fragment reads, 32 consecutive words of
-// one state per half-wave, need no swizzle).  Each lane takes its 16-byte
-// chunk of a row of h at once and feeds its 4 states to 4 consecutive
-// products: product step s of a stage pairs states 8 * (lane / 32) + s across
-// both operands, a fixed permutation of the stage's states, so the sums are
-// the same.
 // Each stage has its own __shared__ array, which lets the compiler see that
 // MFMA-side LDS reads never alias the DMA writes still in flight; the kernel
 // waits on the vector-memory counter itself (s_waitcnt vmcnt).
 #pragma once
 
-#include <type_traits>
-
 #include "k1_common.hpp"
 
 namespace kb {
 
-template <class L, bool F32>
+template <class L>
 struct DmaGeom {
-  static constexpr int BK = F32 ? 16 : 32;      // K per stage: 64 bytes of an h row
-  static constexpr int EPC = F32 ? 4 : 8;       // elements per 16-byte chunk
+  static constexpr int BK = 32;                 // K per stage: 64 bytes of an h row
+  static constexpr int EPC = 8;                 // elements per 16-byte chunk
   static constexpr int NS = 4;                  // stages in the ring
   static constexpr int WCH = L::BV / EPC;       // 16-byte chunks per W row
   static constexpr int W_SLOTS = BK * WCH;      // 16-byte chunks of W per stage
@@ -49,13 +38,13 @@ struct DmaGeom {
   static_assert(W_PER_WAVE % 64 == 0 || W_PER_WAVE < 64, "whole or partial DMA instructions");
   static_assert(H_PER_WAVE % 64 == 0 || H_PER_WAVE < 64, "whole or partial DMA instructions");
   static_assert(WCH >= 16, "the swizzle permutes 16 chunks");
-  static_assert(BK * (F32 ? 4 : 2) == 64, "h rows hold four 16-byte chunks per stage");
+  static_assert(BK * 2 == 64, "h rows hold four 16-byte chunks per stage");
 };
 
-template <class L, int KC, bool F32>
+template <class L, int KC>
 struct DmaKernel {
-  using G = DmaGeom<L, F32>;
-  using E = typename std::conditional<F32, float, uint16_t>::type;
+  using G = DmaGeom<L>;
+  using E = uint16_t;
   static constexpr int BV = L::BV, BH = L::BH, WV = L::WV, WH = L::WH, NWV = L::NWV;
   static constexpr int BK = G::BK;
   // per-tile extras (bias, shared-threshold keys), issued with a tile's first stage
@@ -77,7 +66,7 @@ struct DmaKernel {
       const int s = wave * G::W_PER_WAVE + i * 64 + lane;
       const int r = s / G::WCH, pc = s % G::WCH;
       o.wr[i] = r;
-      o.wc[i] = (F32 ? pc : (pc ^ wswz(r))) * G::EPC;
+      o.wc[i] = (pc ^ wswz(r)) * G::EPC;
     }
 #pragma unroll
     for (int i = 0; i < G::H_OPS; ++i) {
@@ -122,10 +111,6 @@ struct DmaKernel {
   }
 
   __device__ __forceinline__ static void compute(f32x16 (&acc)[WV][WH], const uint16_t* Wb, const uint16_t* Hb) {
-    if constexpr (F32) {
-      compute_f32(acc, reinterpret_cast<const float*>(Wb), reinterpret_cast<const float*>(Hb));
-      return;
-    }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wv = wave % NWV, wh = wave / NWV;
     const int g = lane >> 4, j = lane & 15;
@@ -156,38 +141,6 @@ struct DmaKernel {
           acc[vb][hb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[vb], bf[hb], acc[vb][hb], 0, 0, 0);
     }
   }
-
-  // float32: step 4 c + s (c < 2, s < 4) of the stage pairs, in lane half g,
-  // state 8 g + 4 c + s: A (W, [state][word]) one float per lane, B (h)
-  // element s of the lane's 16-byte chunk 2 g + c of its row
-  __device__ __forceinline__ static void compute_f32(f32x16 (&acc)[WV][WH], const float* Wb, const float* Hb) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wv = wave % NWV, wh = wave / NWV;
-    const int g = lane >> 5, col = lane & 31;
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      float4 hq[WH];
-#pragma unroll
-      for (int hb = 0; hb < WH; ++hb) {
-        const int n = (wh * WH + hb) * 32 + col;
-        hq[hb] = *reinterpret_cast<const float4*>(Hb + (n * 4 + ((2 * g + c) ^ hswz(n))) * 4);
-      }
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int kr = 8 * g + 4 * c + s;
-        float af[WV];
-#pragma unroll
-        for (int vb = 0; vb < WV; ++vb) af[vb] = Wb[kr * BV + (wv * WV + vb) * 32 + col];
-#pragma unroll
-        for (int vb = 0; vb < WV; ++vb)
-#pragma unroll
-          for (int hb = 0; hb < WH; ++hb) {
-            const float bv = s == 0 ? hq[hb].x : (s == 1 ? hq[hb].y : (s == 2 ? hq[hb].z : hq[hb].w));
-            acc[vb][hb] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[vb], bv, acc[vb][hb], 0, 0, 0);
-          }
-      }
-    }
-  }
 };
 
 // Waves per SIMD the compiler must leave registers for: two for the 64-row x
@@ -195,11 +148,11 @@ struct DmaKernel {
 // in the architectural registers, at most 256 per lane in all), else one.
 constexpr int dma_waves_per_eu(int bh, int bv, int kc) { return bh == 64 && bv == 128 && kc <= 8 ? 2 : 1; }
 
-template <class L, int KC, bool F32>
+template <class L, int KC>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(dma_waves_per_eu(L::BH, L::BV, KC))))
 void k1_dma(K1Args a) {
-  using D = DmaKernel<L, KC, F32>;
-  using G = DmaGeom<L, F32>;
+  using D = DmaKernel<L, KC>;
+  using G = DmaGeom<L>;
   constexpr int BV = L::BV, BH = L::BH, WV = L::WV, WH = L::WH, NWV = L::NWV;
   constexpr int WE = G::W_SLOTS * 8, HE = G::H_SLOTS * 8;  // 2-byte units per stage
   // one __shared__ object per stage: W, then h
@@ -288,19 +241,19 @@ void k1_dma(K1Args a) {
 #pragma unroll
       for (int hb = 0; hb < WH; ++hb) tg[hb] = a.share ? ep.tgk[par][(wh * WH + hb) * 32 + col] : 0u;
     }
-    epi.tile(acc, ep, a, h0, vt * BV, vt == vt0, tg, ep.bias[par]);
+    epi.tile(acc, ep, a, h0, vt * BV, vt * BV, vt == vt0, tg, ep.bias[par]);
   }
   epi.finish(ep, a, h0, split);
 }
 
-template <class L, bool F32 = false>
+template <class L>
 hipError_t launch_k1_dma_layout(int kc, dim3 grid, const K1Args& a, hipStream_t st) {
   const dim3 block(256);
   switch (kc) {
-    case 4: k1_dma<L, 4, F32><<<grid, block, 0, st>>>(a); break;
-    case 8: k1_dma<L, 8, F32><<<grid, block, 0, st>>>(a); break;
-    case 12: k1_dma<L, 12, F32><<<grid, block, 0, st>>>(a); break;
-    case 16: k1_dma<L, 16, F32><<<grid, block, 0, st>>>(a); break;
+    case 4: k1_dma<L, 4><<<grid, block, 0, st>>>(a); break;
+    case 8: k1_dma<L, 8><<<grid, block, 0, st>>>(a); break;
+    case 12: k1_dma<L, 12><<<grid, block, 0, st>>>(a); break;
+    case 16: k1_dma<L, 16><<<grid, block, 0, st>>>(a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -3,6 +3,6 @@
 
 namespace kb {
 hipError_t launch_k1_dma_L64(int kc, dim3 grid, const K1Args& a, hipStream_t st) {
-  return launch_k1_dma_layout<LayL64, false>(kc, grid, a, st);
+  return launch_k1_dma_layout<LayL64>(kc, grid, a, st);
 }
 }  // namespace kb

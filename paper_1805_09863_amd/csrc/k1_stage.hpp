@@ -1,0 +1,396 @@
+// K1, register-staged variant: the fused output-layer projection for every
+// shape and alignment, in bf16 and in float32, all on the bf16 matrix cores.
+//
+// Operands go global -> registers -> LDS -> fragments, each step one or more
+// stages ahead of the products:
+//   * 16-byte loads at the elements' own alignment (rows of an odd V or H
+//     start anywhere), in registers for the next NSET stages.  No load needs a
+//     guard: the last stage of an H that is no multiple of a stage starts
+//     early enough to end at H, and its states that earlier stages have had
+//     are made zero in h; the last tile of a ragged V starts early enough to
+//     end at V, and the epilogue masks the words that the tile before has had.
+//     (GUARD: the form for H below a stage, V below a tile or beyond 2^25,
+//     which loads element by element);
+//   * a stage in LDS is GROUPS groups of 16 states.  bf16: 32 states, two
+//     groups.  float32: 16 states, three groups, the pieces of the split
+//     below.  W keeps its V-contiguous rows (16-byte chunks XOR-swizzled by
+//     the row, fragments through the transpose read ds_read_b64_tr_b16); an h
+//     row holds its groups side by side, padded so that 16 rows' fragments
+//     fall on distinct banks;
+//   * two LDS buffers: the fragments of stage g + 1 are read, and stage g + 2
+//     is written to the buffer that stage g left, between the products of
+//     stage g, so a stage has one barrier and waits for nothing it has just
+//     asked for.
+//
+// float32: each operand is split into three bf16 pieces whose sum is the
+// operand exactly (8 + 8 + 8 significant bits: the first truncated, so that it
+// cannot overflow, the second rounded to nearest, the third what is left), and
+// a product is the six piece products of weight 2^-16 and above, each exact,
+// accumulated in float32.  The three left out are below 2^-22 of the product,
+// with signs that do not lean either way; measured against 64 bits the scores'
+// error is no larger than with the float32 matrix instruction, whose sums take
+// a rounding every two states.  Six bf16 products of 32 cycles replace eight
+// float32 ones of 64.
+#pragma once
+
+#include <type_traits>
+
+#include "k1_common.hpp"
+
+namespace kb {
+
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t stage16 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+#define KB_GLOBAL __attribute__((address_space(1)))
+
+template <bool F32>
+struct StageTy;
+template <>
+struct StageTy<false> {
+  using E = uint16_t;
+  typedef stage16 V16 __attribute__((aligned(2)));  // 16 bytes at any element
+  static constexpr int BK = 32, EPC = 8, GROUPS = 2, PRODS = 2;
+  static constexpr int HS = 40;   // elements of an h row in LDS: 2 x 16, padded to 80 bytes
+};
+template <>
+struct StageTy<true> {
+  using E = float;
+  typedef stage16 V16 __attribute__((aligned(4)));
+  static constexpr int BK = 16, EPC = 4, GROUPS = 3, PRODS = 6;
+  static constexpr int HS = 48;   // 3 x 16 elements, 96 bytes: no two of 16 rows share a bank
+};
+
+// (W group, h group) of product p
+template <bool F32>
+__device__ constexpr int prod_w(int p) {
+  constexpr int w[6] = {2, 0, 1, 1, 0, 0};
+  return F32 ? w[p] : p;
+}
+template <bool F32>
+__device__ constexpr int prod_h(int p) {
+  constexpr int h[6] = {0, 2, 1, 0, 1, 0};
+  return F32 ? h[p] : p;
+}
+
+// The three bf16 pieces of two floats, each pair packed.
+__device__ __forceinline__ void split3(uint32_t u0, uint32_t u1, uint32_t (&p)[3]) {
+  p[0] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
+  const f32x2 r = {__uint_as_float(u0) - __uint_as_float(u0 & 0xFFFF0000u),
+                   __uint_as_float(u1) - __uint_as_float(u1 & 0xFFFF0000u)};
+  p[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2));
+  const float t0 = r[0] - __uint_as_float(p[1] << 16), t1 = r[1] - __uint_as_float(p[1] & 0xFFFF0000u);
+  p[2] = __builtin_amdgcn_perm(__float_as_uint(t1), __float_as_uint(t0), 0x07060302u);
+}
+
+template <class L, bool F32>
+struct StageGeom {
+  using T = StageTy<F32>;
+  static constexpr int WCH = L::BV / T::EPC;            // 16-byte chunks per W row
+  static constexpr int W_OPS = T::BK * WCH / 256;       // chunks of W per thread and stage
+  static constexpr int H_SLOTS = L::BH * 4;             // an h row is four chunks
+  static constexpr int H_OPS = (H_SLOTS + 255) / 256;
+  static constexpr int OPS = W_OPS + H_OPS;
+  // Register sets, i.e. stages between a load and its use, which have to cover
+  // a memory round trip (about 1.2 us): 2 for float32 tiles of 128 rows and
+  // more (1,536 cycles of products a stage), else 4, or 8 for the tiles of
+  // few products a stage where the registers allow.
+  static constexpr int NSET = F32 ? (L::BH >= 128 ? 2 : (OPS <= 3 && L::BH == 32 ? 8 : 4)) : (OPS <= 5 ? 8 : 4);
+  static constexpr int WG = 16 * L::BV;                 // elements of a W group
+  static constexpr int WE = T::GROUPS * WG, HE = L::BH * T::HS;
+  static_assert(T::BK * WCH % 256 == 0, "whole chunks per thread");
+  static_assert(H_SLOTS % 256 == 0 || (H_SLOTS < 256 && H_SLOTS % 64 == 0), "whole waves load h");
+  static_assert(L::BV / 8 >= 16, "the swizzle permutes 16 chunks");
+};
+
+// Waves per SIMD the compiler must leave registers for: two for the tiles
+// planned at two workgroups per CU.
+template <class L, int KC>
+constexpr int stage_waves() {
+  return L::BV == 128 && (L::BH == 32 || (L::BH == 64 && KC <= 8)) ? 2 : 1;
+}
+
+template <class L, int KC, bool F32, bool GUARD>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(stage_waves<L, KC>())))
+void k1_stage(K1Args a) {
+  using T = StageTy<F32>;
+  using G = StageGeom<L, F32>;
+  using E = typename T::E;
+  using GP = const KB_GLOBAL E*;
+  constexpr int BV = L::BV, BH = L::BH, WV = L::WV, WH = L::WH, NWV = L::NWV;
+  constexpr int BK = T::BK, EPC = T::EPC, GROUPS = T::GROUPS, NSET = G::NSET, HS = T::HS;
+  constexpr int ESZ = sizeof(E);
+  __shared__ __attribute__((aligned(16))) uint16_t S[2][G::WE + G::HE];
+  __shared__ __attribute__((aligned(16))) SmemEpi<L> ep;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wv = wave % NWV, wh = wave / NWV;
+  const int half = lane >> 5, col = lane & 31;
+  int row_tile, split;
+  k1_cell(a, blockIdx.x, row_tile, split);
+  const int h0 = row_tile * BH;
+  const int vt0 = split * a.tps;
+  const int vt1 = min(vt0 + a.tps, a.n_vtiles);
+  const int H = a.H, V = a.V;
+  // stages of a tile, rounded up to whole register sets; the ones past H do no products
+  const int nk = (H + BK - 1) / BK;
+  const int nkp = (nk + NSET - 1) / NSET * NSET;
+  const int kz = GUARD ? 0 : nk * BK - H;  // states of the last stage that earlier stages have had
+
+  Epilogue<L, KC> epi;
+  epi.init(ep, a.k);
+
+  // ---- loads: chunk i of this thread is W row wr(i), words wc(i).., or, past
+  // the W chunks, states kc.. of h row (tid + 256 i) / 4.  Byte offsets from
+  // the stage's first W row and h column, which are uniform.
+  auto wr = [&](int i) { return (tid + 256 * i) / G::WCH; };
+  auto wc = [&](int i) { return (tid + 256 * i) % G::WCH * EPC; };
+  const int kc = (tid & 3) * EPC;
+  auto hrow = [&](int i) { return min(h0 + ((tid + 256 * i) >> 2), a.N - 1); };  // rows >= N: never written
+  const KB_GLOBAL char* const Wg = (const KB_GLOBAL char*)(const KB_GLOBAL void*)a.W;
+  const KB_GLOBAL char* const Hg = (const KB_GLOBAL char*)(const KB_GLOBAL void*)a.h;
+  const KB_GLOBAL float* const Bg = (const KB_GLOBAL float*)a.b;
+  uint32_t woff[G::W_OPS], hoff[G::H_OPS];
+#pragma unroll
+  for (int i = 0; i < G::W_OPS; ++i) woff[i] = ((uint32_t)wr(i) * (uint32_t)V + (uint32_t)wc(i)) * ESZ;
+#pragma unroll
+  for (int i = 0; i < G::H_OPS; ++i) hoff[i] = ((uint32_t)hrow(i) * (uint32_t)H + (uint32_t)kc) * ESZ;
+  auto tile_v0 = [&](int vt) { return GUARD ? vt * BV : min(vt * BV, V - BV); };
+
+  stage16 R[NSET][G::OPS];
+  int ivt = vt0, ik0 = 0;  // the next stage to load; past the end, the last one again (never used)
+  auto load = [&](stage16 (&r)[G::OPS]) __attribute__((always_inline)) {
+    const int v0 = tile_v0(ivt);
+    if constexpr (GUARD) {
+#pragma unroll
+      for (int i = 0; i < G::OPS; ++i) {
+        const bool w = i < G::W_OPS;
+        E t[EPC];
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) {
+          t[e] = E(0);
+          if (w) {  // rows past H meet states that are zero; words past V are masked
+            t[e] = ((GP)Wg)[(size_t)min(ik0 + wr(i), H - 1) * V + min(v0 + wc(i) + e, V - 1)];
+          } else if ((G::H_SLOTS >= 256 || tid < G::H_SLOTS) && ik0 + kc + e < H) {
+            t[e] = ((GP)Hg)[(size_t)hrow(i - G::W_OPS) * H + ik0 + kc + e];
+          }
+        }
+        r[i] = __builtin_bit_cast(stage16, t);
+      }
+    } else {
+      const int k = min(ik0, H - BK);
+      const KB_GLOBAL char* const wb = Wg + ((size_t)k * V + v0) * ESZ;
+      const KB_GLOBAL char* const hb = Hg + (size_t)k * ESZ;
+#pragma unroll
+      for (int i = 0; i < G::W_OPS; ++i) r[i] = *(const KB_GLOBAL typename T::V16*)(wb + woff[i]);
+#pragma unroll
+      for (int i = 0; i < G::H_OPS; ++i)
+        if (G::H_SLOTS >= 256 || tid < G::H_SLOTS)
+          r[G::W_OPS + i] = *(const KB_GLOBAL typename T::V16*)(hb + hoff[i]);
+    }
+    // (one path for every stage: a branch around the loads would make the
+    // compiler wait for younger ones than it needs)
+    const bool next = ik0 + BK >= nkp * BK;
+    const bool end = next && ivt + 1 >= vt1;
+    ik0 = end ? ik0 : (next ? 0 : ik0 + BK);
+    ivt += next && !end ? 1 : 0;
+  };
+
+  // the last stage's h: states that earlier stages have had become zero
+  auto zero_tail = [&](stage16 (&r)[G::OPS]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = G::W_OPS; i < G::OPS; ++i)
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        uint32_t m;
+        if constexpr (F32)
+          m = kc + d >= kz ? ~0u : 0u;
+        else
+          m = (kc + 2 * d >= kz ? 0xFFFFu : 0u) | (kc + 2 * d + 1 >= kz ? 0xFFFF0000u : 0u);
+        r[i][d] &= m;
+      }
+  };
+
+  // ---- registers -> LDS, in units that fit between products: f32 two per chunk
+  // (two elements each, the second also writes), bf16 one
+  constexpr int UPC = F32 ? 2 : 1;      // units per chunk
+  constexpr int UNITS = UPC * G::OPS;
+  uint32_t piece[3];                    // the first half's pieces, kept for the write
+  auto unit = [&](const stage16 (&r)[G::OPS], uint16_t* buf, int u) __attribute__((always_inline)) {
+    const int i = u / UPC;
+    const bool w = i < G::W_OPS;
+    const int s = tid + 256 * (w ? i : i - G::W_OPS);
+    int at;
+    if (w) {
+      const int rr = s / G::WCH, c = s % G::WCH * EPC;
+      at = rr * BV + (((c >> 3) ^ wswz(rr)) << 3) + (c & 7);
+    } else {
+      at = G::WE + (s >> 2) * HS + kc;
+    }
+    const bool put = w || G::H_SLOTS >= 256 || tid < G::H_SLOTS;
+    if constexpr (F32) {
+      uint32_t q[3];
+      if (u % 2 == 0) {
+        split3(r[i][0], r[i][1], piece);
+      } else {
+        split3(r[i][2], r[i][3], q);
+        const int gs = w ? G::WG : 16;
+        if (put)
+#pragma unroll
+          for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x2*>(buf + at + p * gs) = u32x2{piece[p], q[p]};
+      }
+    } else {
+      if (put) *reinterpret_cast<stage16*>(buf + at) = r[i];
+    }
+  };
+
+  // ---- LDS -> fragments
+  struct Frag {
+    s16x4 lo[GROUPS][WV], hi[GROUPS][WV];
+    bf16x8 b[GROUPS][WH];
+  };
+  Frag F[2];
+  constexpr int RPG = 2 * WV + WH;     // reads per group
+  constexpr int READS = GROUPS * RPG;
+  auto read = [&](const uint16_t* buf, int u, Frag& f) __attribute__((always_inline)) {
+    const int g = u / RPG, x = u % RPG;
+    if (x < WH) {
+      const int n = (wh * WH + x) * 32 + col;
+      f.b[g][x] = *reinterpret_cast<const bf16x8*>(buf + G::WE + n * HS + g * 16 + half * 8);
+    } else {
+      const int vb = (x - WH) >> 1, hi = (x - WH) & 1;
+      const int q = lane >> 4, j = lane & 15;
+      const int r0 = 8 * (q >> 1) + (j >> 2);
+      const int cw = (wv * WV + vb) * 32 + 16 * (q & 1) + 4 * (j & 3);
+      const int at = g * G::WG + (r0 + 4 * hi) * BV + (((cw >> 3) ^ wswz(r0)) << 3) + (cw & 7);  // row r0 + 4: same swizzle
+      const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((KB_LDS s16x4*)(buf + at));
+      if (hi)
+        f.hi[g][vb] = v;
+      else
+        f.lo[g][vb] = v;
+    }
+  };
+
+  f32x16 acc[WV][WH];
+  constexpr int NB = WV * WH, M = T::PRODS * NB;  // products of a stage
+  auto product = [&](const Frag& f, int i) __attribute__((always_inline)) {
+    const int p = i / NB, vb = i % NB / WH, hb = i % NB % WH;
+    const int gw = prod_w<F32>(p), gh = prod_h<F32>(p);
+    const bf16x8 fa =
+        __builtin_bit_cast(bf16x8, __builtin_shufflevector(f.lo[gw][vb], f.hi[gw][vb], 0, 1, 2, 3, 4, 5, 6, 7));
+    acc[vb][hb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, f.b[gh][hb], acc[vb][hb], 0, 0, 0);
+  };
+
+  // ---- one stage: the products of F[B], with the reads of the next stage's
+  // fragments (from the other buffer) and the writes of the stage after it
+  // (into this stage's buffer) spread between them.  LIVE: false past H.
+  auto work = [&](auto bc, auto lc, const stage16 (&r)[G::OPS]) __attribute__((always_inline)) {
+    constexpr int B = decltype(bc)::value;
+    constexpr bool LIVE = decltype(lc)::value;
+#pragma unroll
+    for (int i = 0; i < M; ++i) {
+      if constexpr (LIVE) product(F[B], i);
+      // the reads over the first half of the products, the units over all
+#pragma unroll
+      for (int u = min(2 * i * READS / M, READS); u < min(2 * (i + 1) * READS / M, READS); ++u)
+        read(S[B ^ 1], u, F[B ^ 1]);
+#pragma unroll
+      for (int u = i * UNITS / M; u < (i + 1) * UNITS / M; ++u) unit(r, S[B], u);
+      if constexpr (LIVE) __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // r: the registers of the stage after next; k2: its number in its tile
+  auto stage = [&](auto bc, bool live, stage16 (&r)[G::OPS], int k2) __attribute__((always_inline)) {
+    if (kz != 0 && k2 == nk - 1) zero_tail(r);
+    if (live)
+      work(bc, std::true_type{}, r);
+    else
+      work(bc, std::false_type{}, r);
+    load(r);
+    lds_barrier();
+  };
+
+  // ---- prologue: stages 0 and 1 in LDS, the next NSET in registers
+#pragma unroll
+  for (int s = 0; s < NSET; ++s) load(R[s]);
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    if (kz != 0 && s == nk - 1) zero_tail(R[s]);
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) unit(R[s], S[s], u);
+    load(R[s]);
+  }
+  lds_barrier();
+#pragma unroll
+  for (int u = 0; u < READS; ++u) read(S[0], u, F[0]);
+  lds_barrier();  // every wave has read buffer 0
+
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  for (int vt = vt0; vt < vt1; ++vt) {
+    const int v0 = tile_v0(vt);
+    // the tile's bias and shared thresholds: asked for now, used after its products
+    uint32_t tg[WH];
+    epi.load_shared_thr(a, h0, tg);
+    constexpr int NBIAS = (BV + 255) / 256;
+    float bz[NBIAS];
+#pragma unroll
+    for (int i = 0; i < NBIAS; ++i) bz[i] = Bg[min(v0 + (tid + 256 * i) % BV, V - 1)];
+#pragma unroll
+    for (int vb = 0; vb < WV; ++vb)
+#pragma unroll
+      for (int hb = 0; hb < WH; ++hb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[vb][hb][r] = 0.f;
+
+    for (int kt = 0; kt < nkp; kt += NSET) {
+#pragma unroll
+      for (int s = 0; s < NSET; s += 2) {
+        // stage kt + s writes stage kt + s + 2, of this tile or the next
+        const int k2 = kt + s + 2 < nkp ? kt + s + 2 : 0;
+        stage(I0{}, kt + s < nk, R[(s + 2) % NSET], k2);
+        stage(I1{}, kt + s + 1 < nk, R[(s + 3) % NSET], k2 + 1);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < NBIAS; ++i) ep.bias[0][(tid + 256 * i) % BV] = bz[i];
+    lds_barrier();
+    epi.tile(acc, ep, a, h0, v0, vt * BV, vt == vt0, tg, ep.bias[0]);
+    // the next tile's first fragments again, so that the epilogue need not hold them
+#pragma unroll
+    for (int u = 0; u < READS; ++u) read(S[0], u, F[0]);
+    lds_barrier();  // every wave has read buffer 0
+  }
+  epi.finish(ep, a, h0, split);
+}
+
+template <class L, int KC, bool F32>
+hipError_t launch_k1_stage_kc(bool guard, dim3 grid, const K1Args& a, hipStream_t st) {
+  if constexpr (L::BH == 32 && L::BV == 128) {
+    if (guard) {
+      k1_stage<L, KC, F32, true><<<grid, dim3(256), 0, st>>>(a);
+      return hipGetLastError();
+    }
+  } else if (guard) {
+    return hipErrorInvalidValue;
+  }
+  k1_stage<L, KC, F32, false><<<grid, dim3(256), 0, st>>>(a);
+  return hipGetLastError();
+}
+
+template <class L, bool F32>
+hipError_t launch_k1_stage(int kc, dim3 grid, const K1Args& a, hipStream_t st) {
+  const bool guard = stage_guarded(F32, a.H, a.V);
+  if (!guard && a.V < L::BV) return hipErrorInvalidValue;
+  switch (kc) {
+    case 4: return launch_k1_stage_kc<L, 4, F32>(guard, grid, a, st);
+    case 8: return launch_k1_stage_kc<L, 8, F32>(guard, grid, a, st);
+    case 12: return launch_k1_stage_kc<L, 12, F32>(guard, grid, a, st);
+    case 16: return launch_k1_stage_kc<L, 16, F32>(guard, grid, a, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace kb

@@ -1,0 +1,8 @@
+// Instantiations of the register-staged projection kernel, float32 (split into bf16 pieces), 128-row x 256-word tile.
+#include "k1_stage.hpp"
+
+namespace kb {
+hipError_t launch_k1_stage_f32_L128(int kc, dim3 grid, const K1Args& a, hipStream_t st) {
+  return launch_k1_stage<LayL128, true>(kc, grid, a, st);
+}
+}  // namespace kb

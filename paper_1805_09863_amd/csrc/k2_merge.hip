@@ -152,7 +152,7 @@ __global__ __launch_bounds__(MAXT) void k2_merge(K2Args a) {
 #pragma unroll
       for (int q = 0; q < NQ; ++q) S += st[q].y * __expf(st[q].x - M);
       S = wave_sum(S);
-      const float lse = M + __logf(S);
+      const float lse = M + logf(S);  // (the fast form's error, about 1e-7 of log2 S, was the largest in the result)
       if (a.row_lse != nullptr && lane == 0) a.row_lse[r] = lse;
       const float base = prev_r - lse;
       const float kth = key_score(key[k - 1]);  // running k-th best (-inf before the first chunk)

@@ -56,7 +56,6 @@ struct K1Args {
   int N, H, V, k;
   int tps;            // vocabulary tiles per split
   int n_vtiles;       // vocabulary tiles in total
-  int vec_ok;         // 16-byte vector loads valid for h and W
   float2* stats;      // [P][N]   (max, sum of exp(x - max)) of each split
   int2* lists;        // [P][N][k] (score bits, word) of each split, best first
   uint32_t* gthr;     // [row_tiles * BH] shared per-row threshold keys (order-preserving), zeroed per call
@@ -99,7 +98,10 @@ __device__ __forceinline__ void k1_cell(const K1Args& a, int b, int& row_tile, i
 enum K1Layout { K1_L256 = 0, K1_L128 = 1, K1_L32 = 2, K1_W256 = 3, K1_L32M = 4, K1_L32S = 5, K1_L64 = 6 };
 
 // dma: the LDS-DMA pipeline (bf16, H % 128 == 0, V % 8 == 0, 16-byte aligned h and W);
-// layout K1_W256 (256 x 256 tiles) exists only with it.
+// layout K1_W256 (256 x 256 tiles) exists only with it.  Everything else is staged
+// through registers (k1_stage.hpp), whose tiles are no wider than the vocabulary.
+// stage_guarded: the shapes that kernel takes element by element, with 32 x 128 tiles.
+inline bool stage_guarded(bool f32, int H, int V) { return H < (f32 ? 16 : 32) || V < 128 || V > (1 << 25); }
 hipError_t launch_k1(int bf16, int dma, int layout, int kc, dim3 grid, const K1Args& a, hipStream_t st);
 hipError_t launch_zero_u32(uint32_t* p, int n, hipStream_t st);
 

@@ -14,39 +14,36 @@
 #include "kb_launch.hpp"
 
 namespace kb {
-hipError_t launch_k1_reg_bf16_L256(int kc, dim3 grid, const K1Args& a, hipStream_t st);
-hipError_t launch_k1_reg_bf16_L128(int kc, dim3 grid, const K1Args& a, hipStream_t st);
-hipError_t launch_k1_reg_bf16_L32(int kc, dim3 grid, const K1Args& a, hipStream_t st);
-hipError_t launch_k1_reg_f32_L256(int kc, dim3 grid, const K1Args& a, hipStream_t st);
-hipError_t launch_k1_reg_f32_L128(int kc, dim3 grid, const K1Args& a, hipStream_t st);
-hipError_t launch_k1_reg_f32_L32(int kc, dim3 grid, const K1Args& a, hipStream_t st);
+hipError_t launch_k1_stage_bf16_L256(int kc, dim3 grid, const K1Args& a, hipStream_t st);
+hipError_t launch_k1_stage_bf16_L128(int kc, dim3 grid, const K1Args& a, hipStream_t st);
+hipError_t launch_k1_stage_bf16_L32(int kc, dim3 grid, const K1Args& a, hipStream_t st);
+hipError_t launch_k1_stage_bf16_L32M(int kc, dim3 grid, const K1Args& a, hipStream_t st);
+hipError_t launch_k1_stage_bf16_L32S(int kc, dim3 grid, const K1Args& a, hipStream_t st);
+hipError_t launch_k1_stage_f32_L256(int kc, dim3 grid, const K1Args& a, hipStream_t st);
+hipError_t launch_k1_stage_f32_L128(int kc, dim3 grid, const K1Args& a, hipStream_t st);
+hipError_t launch_k1_stage_f32_L32(int kc, dim3 grid, const K1Args& a, hipStream_t st);
+hipError_t launch_k1_stage_f32_L32M(int kc, dim3 grid, const K1Args& a, hipStream_t st);
+hipError_t launch_k1_stage_f32_L32S(int kc, dim3 grid, const K1Args& a, hipStream_t st);
+hipError_t launch_k1_stage_f32_L64(int kc, dim3 grid, const K1Args& a, hipStream_t st);
 hipError_t launch_k1_dma_L256(int kc, dim3 grid, const K1Args& a, hipStream_t st);
 hipError_t launch_k1_dma_L128(int kc, dim3 grid, const K1Args& a, hipStream_t st);
 hipError_t launch_k1_dma_L32(int kc, dim3 grid, const K1Args& a, hipStream_t st);
-hipError_t launch_k1_reg_bf16_L32M(int kc, dim3 grid, const K1Args& a, hipStream_t st);
-hipError_t launch_k1_reg_bf16_L32S(int kc, dim3 grid, const K1Args& a, hipStream_t st);
-hipError_t launch_k1_reg_f32_L32M(int kc, dim3 grid, const K1Args& a, hipStream_t st);
-hipError_t launch_k1_reg_f32_L32S(int kc, dim3 grid, const K1Args& a, hipStream_t st);
 hipError_t launch_k1_dma_L32M(int kc, dim3 grid, const K1Args& a, hipStream_t st);
 hipError_t launch_k1_dma_L32S(int kc, dim3 grid, const K1Args& a, hipStream_t st);
-hipError_t launch_k1_wide(int kc, dim3 grid, const K1Args& a, hipStream_t st);
-hipError_t launch_k1_dma_f32_L256(int kc, dim3 grid, const K1Args& a, hipStream_t st);
-hipError_t launch_k1_dma_f32_L128(int kc, dim3 grid, const K1Args& a, hipStream_t st);
-hipError_t launch_k1_dma_f32_L32(int kc, dim3 grid, const K1Args& a, hipStream_t st);
-hipError_t launch_k1_dma_f32_L32M(int kc, dim3 grid, const K1Args& a, hipStream_t st);
-hipError_t launch_k1_dma_f32_L32S(int kc, dim3 grid, const K1Args& a, hipStream_t st);
 hipError_t launch_k1_dma_L64(int kc, dim3 grid, const K1Args& a, hipStream_t st);
-hipError_t launch_k1_dma_f32_L64(int kc, dim3 grid, const K1Args& a, hipStream_t st);
+hipError_t launch_k1_wide(int kc, dim3 grid, const K1Args& a, hipStream_t st);
 
+// float32 is always staged through registers, where it is split; dma: bf16
+// operands the LDS DMA pipeline takes
 hipError_t launch_k1(int bf16, int dma, int layout, int kc, dim3 grid, const K1Args& a, hipStream_t st) {
-  if (dma && !bf16) {
+  if (!bf16) {
     switch (layout) {
-      case K1_L256: return launch_k1_dma_f32_L256(kc, grid, a, st);
-      case K1_L128: return launch_k1_dma_f32_L128(kc, grid, a, st);
-      case K1_L32M: return launch_k1_dma_f32_L32M(kc, grid, a, st);
-      case K1_L32S: return launch_k1_dma_f32_L32S(kc, grid, a, st);
-      case K1_L32: return launch_k1_dma_f32_L32(kc, grid, a, st);
-      case K1_L64: return launch_k1_dma_f32_L64(kc, grid, a, st);
+      case K1_L256: return launch_k1_stage_f32_L256(kc, grid, a, st);
+      case K1_L128: return launch_k1_stage_f32_L128(kc, grid, a, st);
+      case K1_L32: return launch_k1_stage_f32_L32(kc, grid, a, st);
+      case K1_L32M: return launch_k1_stage_f32_L32M(kc, grid, a, st);
+      case K1_L32S: return launch_k1_stage_f32_L32S(kc, grid, a, st);
+      case K1_L64: return launch_k1_stage_f32_L64(kc, grid, a, st);
       default: return hipErrorInvalidValue;  // the 256 x 256 tile is bf16 only
     }
   }
@@ -61,21 +58,13 @@ hipError_t launch_k1(int bf16, int dma, int layout, int kc, dim3 grid, const K1A
       default: return launch_k1_dma_L32(kc, grid, a, st);
     }
   }
-  if (bf16) {
-    switch (layout) {
-      case K1_L256: return launch_k1_reg_bf16_L256(kc, grid, a, st);
-      case K1_L128: return launch_k1_reg_bf16_L128(kc, grid, a, st);
-      case K1_L32M: return launch_k1_reg_bf16_L32M(kc, grid, a, st);
-      case K1_L32S: return launch_k1_reg_bf16_L32S(kc, grid, a, st);
-      default: return launch_k1_reg_bf16_L32(kc, grid, a, st);
-    }
-  }
   switch (layout) {
-    case K1_L256: return launch_k1_reg_f32_L256(kc, grid, a, st);
-    case K1_L128: return launch_k1_reg_f32_L128(kc, grid, a, st);
-    case K1_L32M: return launch_k1_reg_f32_L32M(kc, grid, a, st);
-    case K1_L32S: return launch_k1_reg_f32_L32S(kc, grid, a, st);
-    default: return launch_k1_reg_f32_L32(kc, grid, a, st);
+    case K1_L256: return launch_k1_stage_bf16_L256(kc, grid, a, st);
+    case K1_L128: return launch_k1_stage_bf16_L128(kc, grid, a, st);
+    case K1_L32: return launch_k1_stage_bf16_L32(kc, grid, a, st);
+    case K1_L32M: return launch_k1_stage_bf16_L32M(kc, grid, a, st);
+    case K1_L32S: return launch_k1_stage_bf16_L32S(kc, grid, a, st);
+    default: return hipErrorInvalidValue;
   }
 }
 }  // namespace kb
@@ -203,10 +192,11 @@ int splits_for(int row_tiles, int n_vtiles, int per) {
 
 // the layout of the least modelled time among n (ties keep the earlier)
 template <size_t n>
-void pick_by_model(const TileCost (&costs)[n], int N, int H, int V, bool dma, int kc, Plan& p) {
+void pick_by_model(const TileCost (&costs)[n], int N, int H, int V, bool dma, bool staged, int kc, Plan& p) {
   double best = -1.0;
   for (const TileCost& c : costs) {
     if (c.layout == kb::K1_W256 && V < kWideMinCols) continue;
+    if (staged && V < c.BV) continue;
     if (c.layout == kb::K1_L64 && kc > 8) continue;  // fitted at two workgroups per CU
     const int rt = (N + c.BH - 1) / c.BH, nt = (V + c.BV - 1) / c.BV;
     const int per = per_cu(c.layout, dma, kc);
@@ -237,7 +227,8 @@ constexpr long long kFewMaxWeightsBf16 = 64ll << 20;
 // model; the tuning script sets it): 128x256, 256x128, 32x512, 32x256,
 // 32x128, 64x128 on the DMA pipeline (dma), and 256x256 on the bf16 DMA
 // pipeline with V >= 256 (wide_ok).  Other values are ignored.
-void apply_tile_override(bool dma, bool wide_ok, Plan& p) {
+// A tile wider than V words is one of them on the register-staged kernel (max_words).
+void apply_tile_override(bool dma, bool wide_ok, int max_words, Plan& p) {
   const char* e = getenv("KB_TILE");
   int r = 0, w = 0;
   char tail = 0;
@@ -250,7 +241,7 @@ void apply_tile_override(bool dma, bool wide_ok, Plan& p) {
   else if (r == 32 && w == 256) layout = kb::K1_L32M;
   else if (r == 32 && w == 128) layout = kb::K1_L32S;
   else if (r == 64 && w == 128 && dma) layout = kb::K1_L64;
-  if (layout < 0) return;
+  if (layout < 0 || w > max_words) return;
   p.layout = layout;
   p.BH = r;
   p.BV = w;
@@ -258,6 +249,9 @@ void apply_tile_override(bool dma, bool wide_ok, Plan& p) {
 
 Plan make_plan(int dtype, int N, int H, int V, int k, bool dma, bool vec) {
   Plan p{};
+  const bool dma_path = dma && dma_shape(dtype, H, V);
+  const bool staged = dtype == KB_F32 || !dma_path;  // the register-staged kernel, few rows aside
+  const bool guarded = staged && kb::stage_guarded(dtype == KB_F32, H, V);
   const int few_cw = kb::few_chunk_words(dtype == KB_BF16);
   const int few_nt = (V + few_cw - 1) / few_cw, few_p = std::min(few_nt, kTargetCUs);
   const long long few_work = (long long)N * H * V, few_weights = (long long)H * V;
@@ -270,14 +264,18 @@ Plan make_plan(int dtype, int N, int H, int V, int k, bool dma, bool vec) {
     p.layout = kb::K1_FEW;
     p.BH = kb::FEW_ROWS;
     p.BV = few_cw;
-  } else if (dma && dma_shape(dtype, H, V)) {
-    if (dtype == KB_BF16)
-      pick_by_model(kBf16DmaCosts, N, H, V, true, kc_of(k), p);
-    else
-      pick_by_model(kF32DmaCosts, N, H, V, true, kc_of(k), p);
+  } else if (dma_path && dtype == KB_BF16) {
+    pick_by_model(kBf16DmaCosts, N, H, V, true, false, kc_of(k), p);
+  } else if (guarded) {
+    p.layout = kb::K1_L32S;
+    p.BH = 32;
+    p.BV = 128;
   } else if (dtype == KB_F32) {
-    pick_by_model(kF32Costs, N, H, V, false, kc_of(k), p);
-  } else if (N > 192 && dtype == KB_BF16) {
+    if (dma_path)
+      pick_by_model(kF32DmaCosts, N, H, V, true, true, kc_of(k), p);
+    else
+      pick_by_model(kF32Costs, N, H, V, false, true, kc_of(k), p);
+  } else if (N > 192 || (N >= 33 && V < 256)) {
     p.layout = kb::K1_L256;
     p.BH = 256;
     p.BV = 128;
@@ -295,6 +293,7 @@ Plan make_plan(int dtype, int N, int H, int V, int k, bool dma, bool vec) {
     long best = -1;
     for (int i = 0; i < 3; ++i) {
       const int bv = 512 >> i;
+      if (bv > V) continue;
       const int nt = (V + bv - 1) / bv;
       const int pp = nt < kTargetCUs / rt ? nt : kTargetCUs / rt;
       const long cost = (long)((nt + pp - 1) / pp) * (bv + 64);
@@ -306,8 +305,8 @@ Plan make_plan(int dtype, int N, int H, int V, int k, bool dma, bool vec) {
     }
     p.BH = 32;
   }
-  const bool dma_path = dma && dma_shape(dtype, H, V);
-  if (p.layout != kb::K1_FEW) apply_tile_override(dma_path, dtype == KB_BF16 && dma_path && V >= kWideMinCols, p);
+  if (p.layout != kb::K1_FEW && !guarded)
+    apply_tile_override(dma_path, dtype == KB_BF16 && dma_path && V >= kWideMinCols, staged ? V : INT_MAX, p);
   p.kc = kc_of(k);
   p.row_tiles = (N + p.BH - 1) / p.BH;
   p.n_vtiles = (V + p.BV - 1) / p.BV;
@@ -413,7 +412,6 @@ kb_status launch_projection(int dtype, int N, int H, int V, int k, const void* h
   a1.k = k;
   a1.tps = p.tps;
   a1.n_vtiles = p.n_vtiles;
-  a1.vec_ok = vec_ok;
   a1.stats = stats_out ? stats_out : reinterpret_cast<float2*>((char*)ws + p.stats_off);
   a1.lists = lists_out ? lists_out : reinterpret_cast<int2*>((char*)ws + p.lists_off);
   a1.gthr = reinterpret_cast<uint32_t*>((char*)ws + p.gthr_off);
@@ -517,7 +515,6 @@ UfPlan uf_plan(int N, int H, int V, int k) {
   u.a1.k = k;
   u.a1.tps = tps;
   u.a1.n_vtiles = n_vtiles;
-  u.a1.vec_ok = 1;
   u.a1.row_tiles = u.row_tiles;
   u.a1.P = u.P;
   u.a1.grp = u.row_tiles < 4 ? u.row_tiles : 4;

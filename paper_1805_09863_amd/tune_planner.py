@@ -49,6 +49,9 @@ GRIDS = {
     "f32reg": dict(H=(264, 520, 1032, 2056), V=(8000, 30000, 60000),
                    N=(40, 64, 100, 160, 240, 320, 480, 640, 960, 1280),
                    tiles=("128x256", "256x128", "32x512", "32x256", "32x128")),
+    "bf16reg": dict(H=(500, 1000, 2000), V=(8001, 30001, 50001, 90001),
+                    N=(12, 24, 40, 64, 100, 160, 240, 320, 480, 640, 960, 1280, 2560),
+                    tiles=("128x256", "256x128", "32x512", "32x256", "32x128")),
     "bf16": dict(H=(512, 1024, 2048), V=(8000, 30000, 50000, 90000),
                  N=(40, 64, 100, 160, 240, 320, 480, 640, 960, 1280, 2560),
                  tiles=tuple(TILES)),
@@ -79,9 +82,9 @@ def model_words(N: int, V: int, rows: int, words: int, per: int = 1) -> int:
 
 def measure(dtype: str, grid: dict, reps: int, log) -> list:
     ev = HipEvents()
-    code = binding.KB_BF16 if dtype == "bf16" else binding.KB_F32
-    want = {"bf16": ("wide", "dma"), "f32": ("dma",), "f32reg": ("reg",)}[dtype]
-    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    code = binding.KB_BF16 if dtype.startswith("bf16") else binding.KB_F32
+    want = {"bf16": ("wide", "dma"), "f32": ("dma",), "f32reg": ("reg",), "bf16reg": ("reg",)}[dtype]
+    tdt = torch.bfloat16 if dtype.startswith("bf16") else torch.float32
     g = torch.Generator(device="cuda").manual_seed(7)
     rows = []
     for H in grid["H"]:
@@ -190,7 +193,7 @@ def main():
         grid["N"] = tuple(int(x) for x in args.rows.split(","))
     rows = measure(args.dtype, grid, args.reps, log)
     if args.check:
-        code = binding.KB_BF16 if args.dtype == "bf16" else binding.KB_F32
+        code = binding.KB_BF16 if args.dtype.startswith("bf16") else binding.KB_F32
         for x in rows:
             p = binding.kbest_plan(code, x["N"], x["H"], x["V"], 5)
             x["planner"] = f"{p['tile_rows']}x{p['tile_words']}"
