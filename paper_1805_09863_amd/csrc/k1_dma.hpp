@@ -157,7 +157,7 @@ void k1_dma(K1Args a) {
   constexpr int WE = G::W_SLOTS * 8, HE = G::H_SLOTS * 8;  // 2-byte units per stage
   // one __shared__ object per stage: W, then h
   __shared__ __attribute__((aligned(16))) uint16_t S0[WE + HE], S1[WE + HE], S2[WE + HE], S3[WE + HE];
-  __shared__ __attribute__((aligned(16))) SmemEpi<L> ep;
+  __shared__ __attribute__((aligned(16))) SmemEpi<L, KC> ep;
   static_assert(G::NS == 4, "four named stage buffers");
   // DMA accounting: every wave issues OPS instructions per stage, plus 2 with
   // a tile's first stage.  Waiting for "at most 2*OPS outstanding" therefore

@@ -122,7 +122,7 @@ void k1_stage(K1Args a) {
   constexpr int BK = T::BK, EPC = T::EPC, GROUPS = T::GROUPS, NSET = G::NSET, HS = T::HS;
   constexpr int ESZ = sizeof(E);
   __shared__ __attribute__((aligned(16))) uint16_t S[2][G::WE + G::HE];
-  __shared__ __attribute__((aligned(16))) SmemEpi<L> ep;
+  __shared__ __attribute__((aligned(16))) SmemEpi<L, KC> ep;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);

@@ -118,13 +118,6 @@ __device__ __forceinline__ void opaque(f32x16& x) { asm volatile("" : "+a"(x)); 
 __device__ __forceinline__ void done(float x) { asm volatile("" ::"v"(x)); }
 __device__ __forceinline__ void done(int x) { asm volatile("" ::"v"(x)); }
 
-// 64-bit order key of a (score, word) candidate: higher score first, then
-// lower word (the strict-'>' scans of the paper).  -0 is folded into +0 so
-// that equal scores compare equal.
-__device__ __forceinline__ uint64_t cand_key(float x, int word) {
-  return ((uint64_t)f2key(x + 0.0f) << 32) | (uint32_t)~(uint32_t)word;
-}
-
 // Global atomic max and 16-byte load issued from inline assembly: the
 // compiler then adds no waits of its own for them (its conservative
 // vmcnt(0) would also wait for the DMA stages in flight).  The atomic's

@@ -58,6 +58,15 @@ __device__ __forceinline__ float wave_sum(float v) {
   v += dpp_f<kDppMirror>(v);
   return (lane_f(v, 0) + lane_f(v, 16)) + (lane_f(v, 32) + lane_f(v, 48));
 }
+// M + ln S with S = m 2^e, m in [1/2, 1): the hardware logarithm of S itself
+// (log2 S is 15 or so) is off by up to half a unit of 2^-20, the largest error
+// in a row's log-sum-exp; of m it is within 2^-24, and e ln 2 is added in two
+// parts, the first exact.
+__device__ __forceinline__ float log_plus(float M, float S) {
+  const float e = (float)__builtin_amdgcn_frexp_expf(S), l = __builtin_amdgcn_logf(__builtin_amdgcn_frexp_mantf(S));
+  constexpr float kLn2Hi = 0.693115234375f, kLn2Lo = 3.194618494e-5f;  // their sum is ln 2 to float32
+  return fmaf(e, kLn2Hi, M) + fmaf(l, 0.69314718056f, e * kLn2Lo);
+}
 // A candidate of the sentence merge as one 64-bit key (key_of) of its score
 // and flat index: a higher score, then a lower flat index, gives the larger key.
 __device__ __forceinline__ uint64_t cand_key(float score, int flat) { return key_of(score, flat); }
@@ -152,7 +161,7 @@ __global__ __launch_bounds__(MAXT) void k2_merge(K2Args a) {
 #pragma unroll
       for (int q = 0; q < NQ; ++q) S += st[q].y * __expf(st[q].x - M);
       S = wave_sum(S);
-      const float lse = M + logf(S);  // (the fast form's error, about 1e-7 of log2 S, was the largest in the result)
+      const float lse = log_plus(M, S);
       if (a.row_lse != nullptr && lane == 0) a.row_lse[r] = lse;
       const float base = prev_r - lse;
       const float kth = key_score(key[k - 1]);  // running k-th best (-inf before the first chunk)
