@@ -27,10 +27,11 @@
 // AddBias costs nothing; words >= V start at -inf and drop out everywhere):
 //   * per row of the lane: tile max (3-input max tree), then the running
 //     (max, sum) with one rescale per tile (Algorithm 4's identity);
-//   * rows whose tile max reaches max(local k-th best, shared threshold)
-//     append their candidates to a per-row LDS list; the owner thread of the
-//     row inserts them into its sorted k-list (registers) and raises the
-//     thresholds.  Ties are kept by the filter and settled by word index.
+//   * scores that reach max(local k-th best, shared threshold) go to the row's
+//     pool in LDS, found by a bit mask of the lane's passing scores and picked
+//     out one by one (k1_common.hpp); the owner thread of the row inserts them
+//     into its sorted k-list (registers) and raises the thresholds.  Ties are
+//     kept by the filter and settled by word index.
 #pragma once
 
 #include <type_traits>
@@ -38,6 +39,8 @@
 #include "k1_common.hpp"
 
 namespace kb {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float fmax3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
 
@@ -47,8 +50,8 @@ struct WideGeom {
   static constexpr int HE = BH * BK;  // bf16 elements of h per stage
   static constexpr int OPS = 8;       // DMA instructions per wave per stage
   static constexpr int DMA_SLOT0 = 8; // first MFMA (of each 16) followed by a DMA instruction
-  static constexpr int CAPH = 8;      // candidate slots per row and holder per round
-  static constexpr int DONE = 64;     // "no pending candidates" position
+  static constexpr int SEEDS = 32;    // group maxima per row that seed its threshold
+  static constexpr int PC = 24;       // candidates of a row per round
   static constexpr int MS = 16;       // splits that share their running row maxima
 };
 
@@ -56,30 +59,31 @@ struct alignas(16) WideEpi {
   float bias[2][WideGeom::BV];    // bias of the current / next tile (DMA)
   uint32_t tgk[2][WideGeom::BH];  // shared-threshold keys read for the current / next tile (DMA)
   float thr[WideGeom::BH];        // row's local threshold: its k-th best so far, or the seed
-  uint32_t cnt[WideGeom::BH];     // candidates each holder appended to the row this round (one byte each)
-  int flag[4];                    // "a lane could not append" of this and the next round
-  float trash_x[4 * 64];          // per lane: where a score that takes no slot is written
-  uint8_t trash_p[4 * 64];
+  int cnt[WideGeom::BH];          // candidates of the row this round (may exceed PC: the rest waits)
+  int flag[4];                    // "a lane has candidates left" of this and the next round
   union {
-    // positions (0..63), among the holder's scores, of the scores appended this
-    // round per row and holder; the scores themselves go to the idle ring buffer
-    uint8_t p[WideGeom::BH][4][WideGeom::CAPH];
-    float red[WideGeom::BH][16];  // seeds, then the per-holder statistics
+    uint64_t over[WideGeom::BH][9];  // a row's candidates 16 .. PC - 1, and a slot that is nobody's
+    float red[WideGeom::BH][8];      // the per-holder statistics
   } u;
 };
 
-// Candidate scores of a round live in the ring buffer of a tile's last stage
-// (nk is a multiple of 4, so that is always buffer 3): its reads end at the
-// barrier in the middle of that stage, and the next DMA into it is issued in
-// the next tile's first stage, after the epilogue's last barrier.  Slot c of
-// (row r, holder h) is float (4 r + h) * CAPH + (c ^ ((r >> 1) & 7)): the XOR
-// spreads a wave's appends (32 rows x 2 holders, any slot) over 32 banks.
-__device__ __forceinline__ int cand_slot(int r, int h, int c) {
-  return (r * 4 + h) * WideGeom::CAPH + (c ^ ((r >> 1) & 7));
+// The ring buffer of a tile's last stage (nk is a multiple of 4, so that is
+// always buffer 3) is idle during the epilogue: its reads end at the barrier
+// in the middle of that stage, and the next DMA into it is issued in the next
+// tile's first stage, after the epilogue's last barrier.  It holds the seeds
+// (8 chunks of 16 bytes a row, XOR-swizzled), then each row's first 16
+// candidates (rotated by the row): the rows' 128 bytes would otherwise put
+// every other row on the same banks.
+__device__ __forceinline__ uint32_t seed_at(uint32_t buf, int r, int chunk) {
+  return buf + 128u * (uint32_t)r + 16u * (uint32_t)(chunk ^ ((r >> 1) & 7));
 }
-static_assert(WideGeom::CAPH == 8, "the slot swizzle permutes 8 slots");
-static_assert(WideGeom::BH * 4 * WideGeom::CAPH * 4 <= (WideGeom::WE + WideGeom::HE) * 2,
-              "a round's candidate scores fit in one ring buffer");
+__device__ __forceinline__ uint32_t pool_at(uint32_t buf, uint32_t over, int r, int c) {
+  const uint32_t in = buf + 128u * (uint32_t)r + 8u * (uint32_t)((c + (r >> 1)) & 15);
+  const uint32_t out = over + 72u * (uint32_t)r + 8u * (uint32_t)(c - 16);
+  return c < 16 ? in : out;
+}
+static_assert(WideGeom::BH * 128 <= (WideGeom::WE + WideGeom::HE) * 2, "128 bytes a row fit in one ring buffer");
+static_assert(WideGeom::PC == 24, "16 candidates in the ring buffer, 8 beside it");
 
 // Global->LDS DMA with a wave-uniform base (SGPR pair) and a per-lane 32-bit
 // byte offset: lane i copies 16 bytes from base + voff + OFF to LDS byte
@@ -96,7 +100,7 @@ __device__ __forceinline__ void set_m0(uint32_t lds_base) {
 // instructions, not for inline assembly.  The build checks the device
 // assembly of this file for the hazard on every path (isa_check.py).  Here,
 // in the main loop, the base pair is a loop invariant that the compiler keeps
-// in SGPRs; load4_async below guards itself.
+// in SGPRs.
 template <int OFF>
 __device__ __forceinline__ void dma16_off(uint32_t voff, const void* sbase) {
   const uint64_t p = reinterpret_cast<uint64_t>(sbase);
@@ -118,43 +122,12 @@ __device__ __forceinline__ void opaque(f32x16& x) { asm volatile("" : "+a"(x)); 
 __device__ __forceinline__ void done(float x) { asm volatile("" ::"v"(x)); }
 __device__ __forceinline__ void done(int x) { asm volatile("" ::"v"(x)); }
 
-// Global atomic max and 16-byte load issued from inline assembly: the
-// compiler then adds no waits of its own for them (its conservative
-// vmcnt(0) would also wait for the DMA stages in flight).  The atomic's
-// completion is never waited for; the load is waited for with load_wait.
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// Global atomic max issued from inline assembly: the compiler then adds no
+// wait of its own for it (its conservative vmcnt(0) would also wait for the
+// DMA stages in flight).  Its completion is never waited for.
 __device__ __forceinline__ void atomic_umax_nowait(uint32_t* p, uint32_t v) {
   asm volatile("global_atomic_umax %0, %1, off" ::"v"(p), "v"(v) : "memory");
 }
-// 4-byte load from a wave-uniform base (SGPR pair) plus a per-lane byte offset.
-// The base is first copied by a scalar move into a pair of the statement's
-// own (a scalar instruction waits for a VALU write by itself, and a scalar
-// write needs no wait states before the load): the loads run in the
-// epilogue, where register pressure can make the compiler spill the base
-// pair and restore it with v_readlane right before them (unguarded, builds
-// that did so read a stale base and faulted).
-__device__ __forceinline__ uint32_t load4_async(uint32_t voff, const void* sbase) {
-  const uint64_t p = reinterpret_cast<uint64_t>(sbase);
-  const uint64_t u = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(p >> 32)) << 32) |
-                     (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)p);
-  uint32_t v;
-  uint64_t t;
-  asm volatile("s_mov_b64 %1, %3\n\tglobal_load_dword %0, %2, %1" : "=v"(v), "=&s"(t) : "v"(voff), "s"(u));
-  return v;
-}
-// every vector memory operation of the wave done; the registers pass
-// through so that their uses stay behind the wait
-__device__ __forceinline__ void load_wait(uint32_t (&v)[16]) {
-  asm volatile("s_waitcnt vmcnt(0)"
-               : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]),
-                 "+v"(v[8]), "+v"(v[9]), "+v"(v[10]), "+v"(v[11]), "+v"(v[12]), "+v"(v[13]), "+v"(v[14]),
-                 "+v"(v[15]));
-}
-
-__device__ __forceinline__ float max4(const f32x16& x, int q) {
-  return fmaxf(fmax3(x[4 * q], x[4 * q + 1], x[4 * q + 2]), x[4 * q + 3]);
-}
-
 // What the kernel does with its tiles of scores.
 enum WideMode {
   kWideKBest = 0,   // bias, softmax statistics, per-split k-best (the fused step)
@@ -360,7 +333,7 @@ __global__ __launch_bounds__(256, 1) void k1_wide(K1Args a) {
 #pragma unroll
   for (int j = 0; j < KC; ++j) lkey[j] = (j < KC - k) ? ~0ull : 0ull;
   ep.thr[tid] = kNoThr;
-  ep.cnt[tid] = 0u;
+  ep.cnt[tid] = 0;
   if (tid < 4) ep.flag[tid] = 0;
 
   auto publish = [&](float v) {
@@ -376,32 +349,35 @@ __global__ __launch_bounds__(256, 1) void k1_wide(K1Args a) {
   auto epilogue = [&](int ti) {
     const int par = ti & 1;
     const int v0 = (split + ti * a.P) * BV;
-    // the running maxima splits 0..MS-1 have shared for the owner's row
-    // (loaded now, used after the statistics; split-major, so each load of
-    // the wave reads 64 consecutive rows)
-    uint32_t key[G::MS];
+    // the running maxima splits 0..MS-1 have shared for the rows (split-major,
+    // 1 KB a split), into the idle ring buffer: asked for now, used after the
+    // statistics
     if (kShare && ti > 0) {
       const size_t stride = (size_t)a.row_tiles * BH;
 #pragma unroll
-      for (int i = 0; i < G::MS; ++i) key[i] = load4_async(4u * tid, a.gmax + h0 + i * stride);
+      for (int i = 0; i < G::MS / 4; ++i) {
+        const int sp = wave * (G::MS / 4) + i;
+        dma16(a.gmax + sp * stride + h0 + lane * 4, lds_addr(S3) + sp * (BH * 4));
+      }
     }
-    float tmax[4];
+    float tmax[4][2];  // the lane's largest score of each row's two halves
     // statistics (Algorithm 4, one rescale per tile)
 #pragma unroll
     for (int hb = 0; hb < 4; ++hb) {
 #pragma unroll
       for (int vb = 0; vb < 4; ++vb) opaque(acc[vb][hb]);
-      float m0 = fmax3(acc[0][hb][0], acc[0][hb][1], acc[0][hb][2]);
-      float m1 = fmax3(acc[0][hb][3], acc[0][hb][4], acc[0][hb][5]);
 #pragma unroll
-      for (int vb = 0; vb < 4; ++vb)
+      for (int w = 0; w < 2; ++w) {
+        const f32x16 &xa = acc[2 * w][hb], &xb = acc[2 * w + 1][hb];
+        float m0 = fmax3(xa[0], xa[1], xa[2]), m1 = fmax3(xb[0], xb[1], xb[2]);
 #pragma unroll
-        for (int r = (vb == 0 ? 6 : 0); r < 16; r += 4) {
-          m0 = fmax3(m0, acc[vb][hb][r], acc[vb][hb][r + 1]);
-          m1 = fmax3(m1, acc[vb][hb][r + 2], acc[vb][hb][r + 3]);
+        for (int r = 3; r < 15; r += 2) {
+          m0 = fmax3(m0, xa[r], xa[r + 1]);
+          m1 = fmax3(m1, xb[r], xb[r + 1]);
         }
-      const float mx = fmaxf(m0, m1);
-      tmax[hb] = mx;
+        tmax[hb][w] = fmaxf(fmax3(m0, xa[15], m1), xb[15]);
+      }
+      const float mx = fmaxf(tmax[hb][0], tmax[hb][1]);
       if constexpr (!STATS) {
         done(mx);
         continue;
@@ -427,7 +403,11 @@ __global__ __launch_bounds__(256, 1) void k1_wide(K1Args a) {
       // is worked out only where at least k of them beat the row's present
       // threshold (else it cannot raise it): insertion into a right-aligned
       // descending list by median-of-three.
-      load_wait(key);  // long landed: issued before the statistics
+      wait_vm<0>();  // long landed: issued before the statistics
+      lds_barrier();
+      uint32_t key[G::MS];
+#pragma unroll
+      for (int i = 0; i < G::MS; ++i) key[i] = *(KB_LDS const uint32_t*)(uintptr_t)(lds_addr(S3) + 4u * (i * BH + tid));
       const uint32_t tk = max(f2key(ep.thr[tid]), ep.tgk[par][tid]);
       int above = 0;
 #pragma unroll
@@ -451,46 +431,43 @@ __global__ __launch_bounds__(256, 1) void k1_wide(K1Args a) {
       lds_barrier();  // the holders read the raised threshold below
     }
 
-    // first tile of the split: seed each row's threshold.  Every holder finds
-    // the 4 largest of its 16 quad maxima; these 16 distinct scores of the row
-    // are gathered and their k-th largest (k <= 16) is a valid threshold: k
-    // scores of the row are >= it.
+    const uint32_t pool = lds_addr(S3), over = lds_addr(&ep.u.over[0][0]);
+    // first tile of the split: seed each row's threshold.  Every holder gives
+    // the maxima of 8 groups of 8 scores; the k-th largest of the row's 32
+    // (k <= 16) is a valid threshold: k scores of the row are >= it.
     if (ti == 0) {
 #pragma unroll
       for (int hb = 0; hb < 4; ++hb) {
+        const int rl = wh * 128 + hb * 32 + col;
 #pragma unroll
-        for (int vb = 0; vb < 4; ++vb) opaque(acc[vb][hb]);
-        float sv[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+        for (int w = 0; w < 2; ++w) {
+          opaque(acc[2 * w][hb]);
+          opaque(acc[2 * w + 1][hb]);
+          float g[4];
 #pragma unroll
-        for (int vb = 0; vb < 4; ++vb)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            float x = max4(acc[vb][hb], q);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              const float hi = fmaxf(sv[j], x);
-              x = fminf(sv[j], x);
-              sv[j] = hi;
-            }
+          for (int i = 0; i < 4; ++i) {
+            const f32x16& x = acc[2 * w + (i >> 1)][hb];
+            const int r = 8 * (i & 1);
+            g[i] = fmaxf(fmax3(fmax3(x[r], x[r + 1], x[r + 2]), fmax3(x[r + 3], x[r + 4], x[r + 5]), x[r + 6]), x[r + 7]);
           }
-        *reinterpret_cast<float4*>(&ep.u.red[wh * 128 + hb * 32 + col][4 * holder]) =
-            make_float4(sv[0], sv[1], sv[2], sv[3]);
-        done(sv[3]);
+          *(KB_LDS f32x4*)(uintptr_t)seed_at(pool, rl, 2 * holder + w) = f32x4{g[0], g[1], g[2], g[3]};
+          done(g[3]);
+        }
       }
       lds_barrier();
       {
-        // k-th largest of the 16: right-aligned list of KC slots, +inf sentinels first
+        // k-th largest of the 32: right-aligned list of KC slots, +inf sentinels first, by median of three
         float kv[KC];
 #pragma unroll
         for (int j = 0; j < KC; ++j) kv[j] = (j < KC - k) ? INFINITY : -INFINITY;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          float x = ep.u.red[tid][i];
+        for (int c = 0; c < G::SEEDS / 4; ++c) {
+          const f32x4 q = *(KB_LDS const f32x4*)(uintptr_t)seed_at(pool, tid, c);
 #pragma unroll
-          for (int j = 0; j < KC; ++j) {
-            const float hi = fmaxf(kv[j], x);
-            x = fminf(kv[j], x);
-            kv[j] = hi;
+          for (int e = 0; e < 4; ++e) {
+#pragma unroll
+            for (int j = KC - 1; j > 0; --j) kv[j] = __builtin_amdgcn_fmed3f(kv[j - 1], kv[j], q[e]);
+            kv[0] = fmaxf(kv[0], q[e]);
           }
         }
         const float seed = kv[KC - 1];
@@ -501,102 +478,72 @@ __global__ __launch_bounds__(256, 1) void k1_wide(K1Args a) {
       lds_barrier();
     }
 
-    // candidate rounds.  A lane appends, in position order, every score >= the
-    // row's threshold to its own CAPH slots of the row; past CAPH it notes the
-    // first position it could not append and resumes there in the next round,
-    // against the raised threshold.  Quads are skipped unless some lane of the
-    // wave needs them; inside a quad every lane stores each score, to its next
-    // slot or to its own discard slot, so the appends take no branch.
-    int resume[4];
+    // candidate rounds.  Every score >= max(row's threshold, shared threshold)
+    // goes to the row's pool; scores that find the pool full wait for another
+    // round, against the raised threshold.
+    uint32_t left[4][2];  // scores not yet in a pool
 #pragma unroll
-    for (int hb = 0; hb < 4; ++hb) {
-      const int rl = wh * 128 + hb * 32 + col;
-      const float t = fmaxf(ep.thr[rl], key2f(ep.tgk[par][rl]));
-      resume[hb] = tmax[hb] >= t ? 0 : G::DONE;
-    }
+    for (int hb = 0; hb < 4; ++hb) left[hb][0] = left[hb][1] = ~0u;
     for (int round = 0;; ++round) {
-      int ovf = 0;
+      uint32_t any = 0;
 #pragma unroll
       for (int hb = 0; hb < 4; ++hb) {
-        const int rs = resume[hb];
-        if (__builtin_amdgcn_ballot_w64(rs < G::DONE) != 0ull) {
-          const int rl = wh * 128 + hb * 32 + col;
-          // lanes with nothing pending on this row compare against +inf
-          const float t = rs < G::DONE ? fmaxf(ep.thr[rl], key2f(ep.tgk[par][rl])) : INFINITY;
-          int newres = G::DONE, c = 0;
-          // the lane's slots of the row (LDS byte addresses, opaque so that the
-          // per-slot addresses are formed at the store, not kept in registers)
-          uint32_t sx = lds_addr(S3) + 4u * (uint32_t)((rl * 4 + holder) * G::CAPH), sp = lds_addr(&ep.u.p[rl][holder][0]);
-          const int swz = (rl >> 1) & 7;
-          uint32_t tx = lds_addr(&ep.trash_x[tid]), tp = lds_addr(&ep.trash_p[tid]);
-          asm volatile("" : "+v"(sx), "+v"(sp), "+v"(tx), "+v"(tp));
+        const int rl = wh * 128 + hb * 32 + col;
+        const float t = fmaxf(ep.thr[rl], key2f(ep.tgk[par][rl]));
 #pragma unroll
-          for (int vb = 0; vb < 4; ++vb) {
-            opaque(acc[vb][hb]);  // only this block's 16 scores in VGPRs at a time
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              const bool qp = max4(acc[vb][hb], q) >= t && vb * 16 + 4 * q + 3 >= rs;
-              if (__builtin_amdgcn_ballot_w64(qp) != 0ull) {  // a uniform skip for most quads
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                  const int pos = vb * 16 + 4 * q + j;
-                  const float x = acc[vb][hb][4 * q + j];
-                  const bool pred = x >= t && pos >= rs;
-                  const bool room = c < G::CAPH;
-                  newres = (pred && !room) ? min(newres, pos) : newres;
-                  const bool ok = pred && room;
-                  int pv = pos;  // materialized here, not hoisted (64 constants would pin VGPRs)
-                  asm volatile("" : "+v"(pv));
-                  // every lane stores: a score that takes no slot goes to the lane's own
-                  // discard slot, so the appends need no branch
-                  *(KB_LDS float*)(uintptr_t)(ok ? sx + 4 * (c ^ swz) : tx) = x;
-                  *(KB_LDS uint8_t*)(uintptr_t)(ok ? sp + c : tp) = (uint8_t)pv;
-                  c += ok ? 1 : 0;
-                }
-              }
-            }
-            done(c);
+        for (int w = 0; w < 2; ++w) {
+          if (__builtin_amdgcn_ballot_w64(tmax[hb][w] >= t) == 0ull) {
+            left[hb][w] = 0;
+            continue;
           }
-          reinterpret_cast<uint8_t*>(&ep.cnt[rl])[holder] = (uint8_t)c;
-          resume[hb] = newres;
-          ovf |= newres != G::DONE;
-          done(newres);
+          opaque(acc[2 * w][hb]);  // only these blocks' 32 scores in VGPRs at a time
+          opaque(acc[2 * w + 1][hb]);
+          float x[32];
+#pragma unroll
+          for (int i = 0; i < 32; ++i) x[i] = acc[2 * w + i / 16][hb][i % 16];
+          uint32_t m = pass_mask<32>(x, t) & left[hb][w], kept = 0;
+          const int vbase = v0 + wv * 128 + w * 64 + 4 * half;
+          while (__builtin_amdgcn_ballot_w64(m != 0) != 0ull) {
+            const int p = __builtin_clz(m | 1u);
+            const uint32_t bit = 0x80000000u >> p;
+            const float cx = pick<32>(x, p);
+            if (m != 0) {
+              const int at = __hip_atomic_fetch_add(&ep.cnt[rl], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+              const uint64_t key = cand_key(cx, vbase + pos_word(p));  // while the slot is on its way
+              *(KB_LDS uint64_t*)(uintptr_t)pool_at(pool, over, rl, min(at, G::PC)) = key;
+              kept |= at < G::PC ? 0u : bit;
+              m &= ~bit;
+            }
+          }
+          left[hb][w] = kept;
+          any |= kept;
+          done((int)kept);
         }
       }
-      if (ovf) ep.flag[round & 1] = 1;
+      if (any) ep.flag[round & 1] = 1;
       lds_barrier();
       if (tid == 0) ep.flag[(round + 1) & 1] = 0;  // read only after the next barrier
       {
-        const uint32_t cw = ep.cnt[tid];
-        if (cw != 0u) {
-          // the row's candidates, holder after holder, as one sequence: the
-          // wave loops as long as its longest row, not its longest holder of
-          // each holder in turn
-          const int c0 = cw & 0xFF, c1 = (cw >> 8) & 0xFF, c2 = (cw >> 16) & 0xFF;
-          const int e1 = c0, e2 = c0 + c1, e3 = e2 + c2, tot = e3 + (int)(cw >> 24);
-          for (int i = 0; i < tot; ++i) {
-            const int hd = (i >= e1 ? 1 : 0) + (i >= e2 ? 1 : 0) + (i >= e3 ? 1 : 0);
-            const int j = i - (hd == 0 ? 0 : (hd == 1 ? e1 : (hd == 2 ? e2 : e3)));
-            const int p = ep.u.p[tid][hd][j];
-            const float cx = *(KB_LDS const float*)(uintptr_t)(lds_addr(S3) + 4u * (uint32_t)cand_slot(tid, hd, j));
-            // word of position p of holder hd: holder = 2 wv + half
-            const int word = v0 + (hd >> 1) * 128 + (hd & 1) * 4 + (p >> 4) * 32 + ((p >> 2) & 3) * 8 + (p & 3);
-            uint64_t key = cand_key(cx, word);
-            {
-              rowbest = key > lkey[KC - 1] ? fmaxf(rowbest, cx) : rowbest;
-              // insertion with independent compares, without a branch: the keys
-              // are descending, so gt[] is false then true and the key lands at
-              // the first true; a key below the k-th leaves gt[] all false and
-              // the list unchanged
-              bool gt[KC];
+        const int c = min(ep.cnt[tid], G::PC);
+        if (c > 0) {
+          uint64_t key = *(KB_LDS const uint64_t*)(uintptr_t)pool_at(pool, over, tid, 0);
+          for (int i = 0; i < c; ++i) {
+            // the next key is read while this one is inserted
+            const uint64_t nkey = *(KB_LDS const uint64_t*)(uintptr_t)pool_at(pool, over, tid, min(i + 1, G::PC));
+            rowbest = fmaxf(rowbest, key2f((uint32_t)(key >> 32)));
+            // insertion with independent compares, without a branch: the keys
+            // are descending, so gt[] is false then true and the key lands at
+            // the first true; a key below the k-th leaves gt[] all false and
+            // the list unchanged
+            bool gt[KC];
 #pragma unroll
-              for (int jj = 0; jj < KC; ++jj) gt[jj] = key > lkey[jj];
+            for (int jj = 0; jj < KC; ++jj) gt[jj] = key > lkey[jj];
 #pragma unroll
-              for (int jj = KC - 1; jj > 0; --jj) lkey[jj] = gt[jj] ? (gt[jj - 1] ? lkey[jj - 1] : key) : lkey[jj];
-              lkey[0] = gt[0] ? key : lkey[0];
-            }
+            for (int jj = KC - 1; jj > 0; --jj) lkey[jj] = gt[jj] ? (gt[jj - 1] ? lkey[jj - 1] : key) : lkey[jj];
+            lkey[0] = gt[0] ? key : lkey[0];
+            key = nkey;
           }
-          ep.cnt[tid] = 0u;
+          ep.cnt[tid] = 0;
         }
         const float kth = key2f((uint32_t)(lkey[KC - 1] >> 32));
         if (kth > ep.thr[tid]) ep.thr[tid] = kth;
