@@ -38,9 +38,10 @@
  *  - The projection's tile is chosen by a cost model (kb_kbest_plan reports
  *    the choice).  With the environment variable KB_TILE=<rows>x<words> at
  *    call time (e.g. 32x256) a step not taken by the few-row kernel uses that
- *    tile instead where its path has it: 128x256, 256x128, 32x512, 32x256
- *    or 32x128 on every path, 64x128 on the DMA pipeline, and 256x256 on the
- *    bf16 DMA pipeline with V >= 256.  Other values are ignored.  It exists to measure the
+ *    tile instead where its path has it: 128x256, 256x128, 32x512, 32x256,
+ *    32x128 or 64x256 on every path, 64x128 on KB_KERNEL_DMA shapes, and
+ *    256x256 on bf16 ones with V >= 256.  Other values are ignored, and on the
+ *    register-staged kernel tiles wider than V.  It exists to measure the
  *    model (paper_1805_09863_amd/tune_planner.py); the workspace size follows
  *    it, so size the workspace with the same setting.
  *  - Size limits (KB_ERR_UNSUPPORTED beyond them): N * V <= INT_MAX (a
@@ -105,16 +106,20 @@ size_t kb_kbest_workspace_bytes(int dtype, int N, int H, int V, int k, int S);
  *     [KB_PLAN_TILE_ROWS]        rows per tile (KB_KERNEL_FEW: rows it holds)
  *     [KB_PLAN_TILE_WORDS]       words per tile (KB_KERNEL_FEW: per chunk)
  *     [KB_PLAN_ROW_TILES]        ceil(N / rows per tile)
- *     [KB_PLAN_SPLITS]           P, each split a run of whole tiles
- *     [KB_PLAN_TILES_PER_SPLIT]  tiles in each split (the last may be short)
+ *     [KB_PLAN_SPLITS]           P; a split is every P-th tile (few-row
+ *                                kernel: a run of chunks)
+ *     [KB_PLAN_TILES_PER_SPLIT]  tiles in each split (some have one less)
  * Errors: the shape checks of kb_kbest_step (KB_ERR_INVALID_ARG,
  * KB_ERR_UNSUPPORTED); KB_ERR_INVALID_ARG for a null plan_out or for h, W or
  * b not aligned to their element size.
  */
 #define KB_KERNEL_FEW 0  /* vector ALUs, W streamed once (a few rows)          */
 #define KB_KERNEL_WIDE 1 /* 256 x 256 tiles, matrix cores, LDS DMA pipeline   */
-#define KB_KERNEL_DMA 2  /* other tiles on the matrix cores, LDS DMA pipeline */
-#define KB_KERNEL_REG 3  /* matrix cores, operands staged through registers  */
+#define KB_KERNEL_DMA 2  /* other tiles on the matrix cores, 16-byte aligned     */
+                         /* shapes: bf16 the LDS DMA pipeline, float32 (split    */
+                         /* into bf16 pieces) staged through registers           */
+#define KB_KERNEL_REG 3  /* matrix cores, operands staged through registers,  */
+                         /* any shape and alignment                              */
 #define KB_PLAN_KERNEL 0
 #define KB_PLAN_TILE_ROWS 1
 #define KB_PLAN_TILE_WORDS 2

@@ -167,10 +167,13 @@ void k1_dma(K1Args a) {
   int row_tile, split;
   k1_cell(a, blockIdx.x, row_tile, split);
   const int h0 = row_tile * BH;
-  const int vt0 = split * a.tps;
-  const int vt1 = min(vt0 + a.tps, a.n_vtiles);
   const int nk = a.H / G::BK;  // a multiple of 4: every tile starts on ring buffer 0
-  const int total = (vt1 - vt0) * nk;
+  // the split's tiles are split, split + P, split + 2 P, ...: the workgroups
+  // running at one time then read neighbouring pieces of the same rows of W
+  // (runs of tiles, which leave gaps between them, took up to twice as long:
+  // 320 rows, H = 512, V = 90,000, 64 x 128 tiles), and a skewed prior's high
+  // scores come early in every split
+  const int total = (a.n_vtiles - split + a.P - 1) / a.P * nk;
   const uint32_t sbuf[4] = {lds_addr(S0), lds_addr(S1), lds_addr(S2), lds_addr(S3)};
 
   Epilogue<L, KC> epi;
@@ -179,7 +182,7 @@ void k1_dma(K1Args a) {
   D::offsets(offs, a, h0);
 
   // next stage to issue: tile start iv0 (tile index it), state offset ik0
-  int iv0 = vt0 * BV, ik0 = 0, it = 0, issued = 0;
+  int iv0 = split * BV, ik0 = 0, it = 0, issued = 0;
   auto issue_next = [&](int buf) {
     if (issued < total) {
       D::issue(a, offs, sbuf[buf], iv0, ik0, lds_addr(&ep.bias[it & 1][0]), lds_addr(&ep.tgk[it & 1][0]));
@@ -187,7 +190,7 @@ void k1_dma(K1Args a) {
       ik0 += G::BK;
       if (ik0 == a.H) {
         ik0 = 0;
-        iv0 += BV;
+        iv0 += a.P * BV;
         ++it;
       }
     }
@@ -211,7 +214,7 @@ void k1_dma(K1Args a) {
   };
 
   int g = 0;
-  for (int vt = vt0; vt < vt1; ++vt) {
+  for (int vt = split, ti = 0; vt < a.n_vtiles; vt += a.P, ++ti) {
     f32x16 acc[WV][WH];
 #pragma unroll
     for (int vb = 0; vb < WV; ++vb)
@@ -234,14 +237,14 @@ void k1_dma(K1Args a) {
       D::compute(acc, S3, S3 + WE);
     }
     // this tile's bias and keys landed with its first stage (waited for above)
-    const int par = (vt - vt0) & 1;
+    const int par = ti & 1;
     uint32_t tg[WH];
     {
       const int wh = wave / NWV, col = lane & 31;
 #pragma unroll
       for (int hb = 0; hb < WH; ++hb) tg[hb] = a.share ? ep.tgk[par][(wh * WH + hb) * 32 + col] : 0u;
     }
-    epi.tile(acc, ep, a, h0, vt * BV, vt * BV, vt == vt0, tg, ep.bias[par]);
+    epi.tile(acc, ep, a, h0, vt * BV, vt * BV, ti == 0, tg, ep.bias[par]);
   }
   epi.finish(ep, a, h0, split);
 }

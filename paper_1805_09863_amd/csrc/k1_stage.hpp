@@ -74,14 +74,17 @@ __device__ constexpr int prod_h(int p) {
   return F32 ? h[p] : p;
 }
 
-// The three bf16 pieces of two floats, each pair packed.
-__device__ __forceinline__ void split3(uint32_t u0, uint32_t u1, uint32_t (&p)[3]) {
-  p[0] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
-  const f32x2 r = {__uint_as_float(u0) - __uint_as_float(u0 & 0xFFFF0000u),
-                   __uint_as_float(u1) - __uint_as_float(u1 & 0xFFFF0000u)};
-  p[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2));
-  const float t0 = r[0] - __uint_as_float(p[1] << 16), t1 = r[1] - __uint_as_float(p[1] & 0xFFFF0000u);
-  p[2] = __builtin_amdgcn_perm(__float_as_uint(t1), __float_as_uint(t0), 0x07060302u);
+// The three bf16 pieces of two floats, each pair packed, in two parts of five
+// and six instructions: the first piece and what it leaves, then the other two.
+__device__ __forceinline__ void split_first(uint32_t u0, uint32_t u1, uint32_t& p0, f32x2& rest) {
+  p0 = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
+  rest = f32x2{__uint_as_float(u0) - __uint_as_float(u0 & 0xFFFF0000u),
+               __uint_as_float(u1) - __uint_as_float(u1 & 0xFFFF0000u)};
+}
+__device__ __forceinline__ void split_rest(f32x2 r, uint32_t& p1, uint32_t& p2) {
+  p1 = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2));
+  const float t0 = r[0] - __uint_as_float(p1 << 16), t1 = r[1] - __uint_as_float(p1 & 0xFFFF0000u);
+  p2 = __builtin_amdgcn_perm(__float_as_uint(t1), __float_as_uint(t0), 0x07060302u);
 }
 
 template <class L, bool F32>
@@ -100,7 +103,9 @@ struct StageGeom {
   static constexpr int WG = 16 * L::BV;                 // elements of a W group
   static constexpr int WE = T::GROUPS * WG, HE = L::BH * T::HS;
   static_assert(T::BK * WCH % 256 == 0, "whole chunks per thread");
-  static_assert(H_SLOTS % 256 == 0 || (H_SLOTS < 256 && H_SLOTS % 64 == 0), "whole waves load h");
+  // (32 rows: two threads load, split and write the same chunk, which costs
+  // less than a branch)
+  static_assert(H_SLOTS % 256 == 0 || H_SLOTS == 128, "whole waves load h");
   static_assert(L::BV / 8 >= 16, "the swizzle permutes 16 chunks");
 };
 
@@ -131,13 +136,10 @@ void k1_stage(K1Args a) {
   int row_tile, split;
   k1_cell(a, blockIdx.x, row_tile, split);
   const int h0 = row_tile * BH;
-  const int vt0 = split * a.tps;
-  const int vt1 = min(vt0 + a.tps, a.n_vtiles);
   const int H = a.H, V = a.V;
-  // stages of a tile, rounded up to whole register sets; the ones past H do no products
+  // stages of a tile, rounded up to whole register sets; those past H meet states of zero
   const int nk = (H + BK - 1) / BK;
   const int nkp = (nk + NSET - 1) / NSET * NSET;
-  const int kz = GUARD ? 0 : nk * BK - H;  // states of the last stage that earlier stages have had
 
   Epilogue<L, KC> epi;
   epi.init(ep, a.k);
@@ -148,7 +150,8 @@ void k1_stage(K1Args a) {
   auto wr = [&](int i) { return (tid + 256 * i) / G::WCH; };
   auto wc = [&](int i) { return (tid + 256 * i) % G::WCH * EPC; };
   const int kc = (tid & 3) * EPC;
-  auto hrow = [&](int i) { return min(h0 + ((tid + 256 * i) >> 2), a.N - 1); };  // rows >= N: never written
+  auto hslot = [&](int i) { return (tid + 256 * i) % G::H_SLOTS >> 2; };
+  auto hrow = [&](int i) { return min(h0 + hslot(i), a.N - 1); };  // rows >= N: never written
   const KB_GLOBAL char* const Wg = (const KB_GLOBAL char*)(const KB_GLOBAL void*)a.W;
   const KB_GLOBAL char* const Hg = (const KB_GLOBAL char*)(const KB_GLOBAL void*)a.h;
   const KB_GLOBAL float* const Bg = (const KB_GLOBAL float*)a.b;
@@ -160,89 +163,95 @@ void k1_stage(K1Args a) {
   auto tile_v0 = [&](int vt) { return GUARD ? vt * BV : min(vt * BV, V - BV); };
 
   stage16 R[NSET][G::OPS];
-  int ivt = vt0, ik0 = 0;  // the next stage to load; past the end, the last one again (never used)
-  auto load = [&](stage16 (&r)[G::OPS]) __attribute__((always_inline)) {
-    const int v0 = tile_v0(ivt);
+  // the split's tiles are split, split + P, split + 2 P, ... (as in the DMA kernel)
+  int ivt = split, ik0 = 0;  // the next stage to load; past the end, the last one again (never used)
+  const KB_GLOBAL char *wb, *hb;  // its first W row and h column
+  auto set_base = [&]() {
+    const int k = GUARD ? ik0 : min(ik0, H - BK);
+    wb = Wg + ((size_t)k * V + tile_v0(ivt)) * ESZ;
+    hb = Hg + (size_t)k * ESZ;
+  };
+  set_base();
+  // (one path for every stage: a branch around the loads would make the
+  // compiler wait for younger ones than it needs)
+  auto load = [&](stage16 (&r)[G::OPS], int i) __attribute__((always_inline)) {
+    const bool w = i < G::W_OPS;
     if constexpr (GUARD) {
+      E t[EPC];
 #pragma unroll
-      for (int i = 0; i < G::OPS; ++i) {
-        const bool w = i < G::W_OPS;
-        E t[EPC];
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) {
-          t[e] = E(0);
-          if (w) {  // rows past H meet states that are zero; words past V are masked
-            t[e] = ((GP)Wg)[(size_t)min(ik0 + wr(i), H - 1) * V + min(v0 + wc(i) + e, V - 1)];
-          } else if ((G::H_SLOTS >= 256 || tid < G::H_SLOTS) && ik0 + kc + e < H) {
-            t[e] = ((GP)Hg)[(size_t)hrow(i - G::W_OPS) * H + ik0 + kc + e];
-          }
-        }
-        r[i] = __builtin_bit_cast(stage16, t);
+      for (int e = 0; e < EPC; ++e) {
+        t[e] = E(0);
+        if (w)  // rows past H meet states that are zero; words past V are masked
+          t[e] = ((GP)Wg)[(size_t)min(ik0 + wr(i), H - 1) * V + min(tile_v0(ivt) + wc(i) + e, V - 1)];
+        else if (ik0 + kc + e < H)
+          t[e] = ((GP)Hg)[(size_t)hrow(i - G::W_OPS) * H + ik0 + kc + e];
       }
+      r[i] = __builtin_bit_cast(stage16, t);
     } else {
-      const int k = min(ik0, H - BK);
-      const KB_GLOBAL char* const wb = Wg + ((size_t)k * V + v0) * ESZ;
-      const KB_GLOBAL char* const hb = Hg + (size_t)k * ESZ;
-#pragma unroll
-      for (int i = 0; i < G::W_OPS; ++i) r[i] = *(const KB_GLOBAL typename T::V16*)(wb + woff[i]);
-#pragma unroll
-      for (int i = 0; i < G::H_OPS; ++i)
-        if (G::H_SLOTS >= 256 || tid < G::H_SLOTS)
-          r[G::W_OPS + i] = *(const KB_GLOBAL typename T::V16*)(hb + hoff[i]);
+      r[i] = *(const KB_GLOBAL typename T::V16*)(w ? wb + woff[i] : hb + hoff[i - G::W_OPS]);
     }
-    // (one path for every stage: a branch around the loads would make the
-    // compiler wait for younger ones than it needs)
+  };
+  auto next_stage = [&]() {
     const bool next = ik0 + BK >= nkp * BK;
-    const bool end = next && ivt + 1 >= vt1;
+    const bool end = next && ivt + a.P >= a.n_vtiles;
     ik0 = end ? ik0 : (next ? 0 : ik0 + BK);
-    ivt += next && !end ? 1 : 0;
+    ivt += next && !end ? a.P : 0;
+    set_base();
   };
 
-  // the last stage's h: states that earlier stages have had become zero
-  auto zero_tail = [&](stage16 (&r)[G::OPS]) __attribute__((always_inline)) {
+  // stage k2 >= nk - 1 of a tile: states that earlier stages have had, the
+  // first z of it, become zero (the guarded loads give zeros themselves)
+  auto zero_tail = [&](stage16 (&r)[G::OPS], int k2) __attribute__((always_inline)) {
+    if (GUARD || (k2 + 1) * BK <= H) return;
+    const int z = (k2 + 1) * BK - H;
 #pragma unroll
     for (int i = G::W_OPS; i < G::OPS; ++i)
 #pragma unroll
       for (int d = 0; d < 4; ++d) {
         uint32_t m;
         if constexpr (F32)
-          m = kc + d >= kz ? ~0u : 0u;
+          m = kc + d >= z ? ~0u : 0u;
         else
-          m = (kc + 2 * d >= kz ? 0xFFFFu : 0u) | (kc + 2 * d + 1 >= kz ? 0xFFFF0000u : 0u);
+          m = (kc + 2 * d >= z ? 0xFFFFu : 0u) | (kc + 2 * d + 1 >= z ? 0xFFFF0000u : 0u);
         r[i][d] &= m;
       }
   };
 
-  // ---- registers -> LDS, in units that fit between products: f32 two per chunk
-  // (two elements each, the second also writes), bf16 one
-  constexpr int UPC = F32 ? 2 : 1;      // units per chunk
-  constexpr int UNITS = UPC * G::OPS;
-  uint32_t piece[3];                    // the first half's pieces, kept for the write
-  auto unit = [&](const stage16 (&r)[G::OPS], uint16_t* buf, int u) __attribute__((always_inline)) {
-    const int i = u / UPC;
+  // ---- registers -> LDS -> the registers' next load, in steps that fit
+  // between products (seven VALU instructions hide behind one): per chunk of
+  // 16 bytes two splits of two parts each, the write of three pieces, the load
+  // (float32), or the write and the load (bf16)
+  constexpr int STEPS = F32 ? 6 : 2, UNITS = STEPS * G::OPS;
+  uint32_t piece[3][2];
+  f32x2 rest;
+  auto unit = [&](stage16 (&r)[G::OPS], uint16_t* buf, int u) __attribute__((always_inline)) {
+    const int i = u / STEPS, step = u % STEPS;
+    if (step == STEPS - 1) {
+      load(r, i);
+      return;
+    }
+    if (F32 && step < 4) {
+      const int e = step >> 1;
+      if ((step & 1) == 0)
+        split_first(r[i][2 * e], r[i][2 * e + 1], piece[0][e], rest);
+      else
+        split_rest(rest, piece[1][e], piece[2][e]);
+      return;
+    }
     const bool w = i < G::W_OPS;
-    const int s = tid + 256 * (w ? i : i - G::W_OPS);
     int at;
     if (w) {
-      const int rr = s / G::WCH, c = s % G::WCH * EPC;
+      const int rr = wr(i), c = wc(i);
       at = rr * BV + (((c >> 3) ^ wswz(rr)) << 3) + (c & 7);
     } else {
-      at = G::WE + (s >> 2) * HS + kc;
+      at = G::WE + hslot(i - G::W_OPS) * HS + kc;
     }
-    const bool put = w || G::H_SLOTS >= 256 || tid < G::H_SLOTS;
     if constexpr (F32) {
-      uint32_t q[3];
-      if (u % 2 == 0) {
-        split3(r[i][0], r[i][1], piece);
-      } else {
-        split3(r[i][2], r[i][3], q);
-        const int gs = w ? G::WG : 16;
-        if (put)
+      const int gs = w ? G::WG : 16;
 #pragma unroll
-          for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x2*>(buf + at + p * gs) = u32x2{piece[p], q[p]};
-      }
+      for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x2*>(buf + at + p * gs) = u32x2{piece[p][0], piece[p][1]};
     } else {
-      if (put) *reinterpret_cast<stage16*>(buf + at) = r[i];
+      *reinterpret_cast<stage16*>(buf + at) = r[i];
     }
   };
 
@@ -284,43 +293,40 @@ void k1_stage(K1Args a) {
   };
 
   // ---- one stage: the products of F[B], with the reads of the next stage's
-  // fragments (from the other buffer) and the writes of the stage after it
-  // (into this stage's buffer) spread between them.  LIVE: false past H.
-  auto work = [&](auto bc, auto lc, const stage16 (&r)[G::OPS]) __attribute__((always_inline)) {
+  // fragments (from the other buffer), the writes of the stage after it (into
+  // this stage's buffer) and the loads that follow them spread between them.
+  // r: the registers of the stage after next; k2: its number in its tile
+  auto stage = [&](auto bc, stage16 (&r)[G::OPS], int k2) __attribute__((always_inline)) {
     constexpr int B = decltype(bc)::value;
-    constexpr bool LIVE = decltype(lc)::value;
+    zero_tail(r, k2);
 #pragma unroll
     for (int i = 0; i < M; ++i) {
-      if constexpr (LIVE) product(F[B], i);
+      product(F[B], i);
       // the reads over the first half of the products, the units over all
 #pragma unroll
       for (int u = min(2 * i * READS / M, READS); u < min(2 * (i + 1) * READS / M, READS); ++u)
         read(S[B ^ 1], u, F[B ^ 1]);
 #pragma unroll
       for (int u = i * UNITS / M; u < (i + 1) * UNITS / M; ++u) unit(r, S[B], u);
-      if constexpr (LIVE) __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_sched_barrier(0);
     }
-  };
-  // r: the registers of the stage after next; k2: its number in its tile
-  auto stage = [&](auto bc, bool live, stage16 (&r)[G::OPS], int k2) __attribute__((always_inline)) {
-    if (kz != 0 && k2 == nk - 1) zero_tail(r);
-    if (live)
-      work(bc, std::true_type{}, r);
-    else
-      work(bc, std::false_type{}, r);
-    load(r);
+    next_stage();
     lds_barrier();
   };
 
   // ---- prologue: stages 0 and 1 in LDS, the next NSET in registers
 #pragma unroll
-  for (int s = 0; s < NSET; ++s) load(R[s]);
+  for (int s = 0; s < NSET; ++s) {
+#pragma unroll
+    for (int i = 0; i < G::OPS; ++i) load(R[s], i);
+    next_stage();
+  }
 #pragma unroll
   for (int s = 0; s < 2; ++s) {
-    if (kz != 0 && s == nk - 1) zero_tail(R[s]);
+    zero_tail(R[s], s);
 #pragma unroll
     for (int u = 0; u < UNITS; ++u) unit(R[s], S[s], u);
-    load(R[s]);
+    next_stage();
   }
   lds_barrier();
 #pragma unroll
@@ -329,7 +335,7 @@ void k1_stage(K1Args a) {
 
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
-  for (int vt = vt0; vt < vt1; ++vt) {
+  for (int vt = split; vt < a.n_vtiles; vt += a.P) {
     const int v0 = tile_v0(vt);
     // the tile's bias and shared thresholds: asked for now, used after its products
     uint32_t tg[WH];
@@ -350,14 +356,14 @@ void k1_stage(K1Args a) {
       for (int s = 0; s < NSET; s += 2) {
         // stage kt + s writes stage kt + s + 2, of this tile or the next
         const int k2 = kt + s + 2 < nkp ? kt + s + 2 : 0;
-        stage(I0{}, kt + s < nk, R[(s + 2) % NSET], k2);
-        stage(I1{}, kt + s + 1 < nk, R[(s + 3) % NSET], k2 + 1);
+        stage(I0{}, R[(s + 2) % NSET], k2);
+        stage(I1{}, R[(s + 3) % NSET], k2 + 1);
       }
     }
 #pragma unroll
     for (int i = 0; i < NBIAS; ++i) ep.bias[0][(tid + 256 * i) % BV] = bz[i];
     lds_barrier();
-    epi.tile(acc, ep, a, h0, v0, vt * BV, vt == vt0, tg, ep.bias[0]);
+    epi.tile(acc, ep, a, h0, v0, vt * BV, vt == split, tg, ep.bias[0]);
     // the next tile's first fragments again, so that the epilogue need not hold them
 #pragma unroll
     for (int u = 0; u < READS; ++u) read(S[0], u, F[0]);

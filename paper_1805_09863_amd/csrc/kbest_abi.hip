@@ -31,6 +31,9 @@ hipError_t launch_k1_dma_L32(int kc, dim3 grid, const K1Args& a, hipStream_t st)
 hipError_t launch_k1_dma_L32M(int kc, dim3 grid, const K1Args& a, hipStream_t st);
 hipError_t launch_k1_dma_L32S(int kc, dim3 grid, const K1Args& a, hipStream_t st);
 hipError_t launch_k1_dma_L64(int kc, dim3 grid, const K1Args& a, hipStream_t st);
+hipError_t launch_k1_stage_bf16_L64M(int kc, dim3 grid, const K1Args& a, hipStream_t st);
+hipError_t launch_k1_stage_f32_L64M(int kc, dim3 grid, const K1Args& a, hipStream_t st);
+hipError_t launch_k1_dma_L64M(int kc, dim3 grid, const K1Args& a, hipStream_t st);
 hipError_t launch_k1_wide(int kc, dim3 grid, const K1Args& a, hipStream_t st);
 
 // float32 is always staged through registers, where it is split; dma: bf16
@@ -44,6 +47,7 @@ hipError_t launch_k1(int bf16, int dma, int layout, int kc, dim3 grid, const K1A
       case K1_L32M: return launch_k1_stage_f32_L32M(kc, grid, a, st);
       case K1_L32S: return launch_k1_stage_f32_L32S(kc, grid, a, st);
       case K1_L64: return launch_k1_stage_f32_L64(kc, grid, a, st);
+      case K1_L64M: return launch_k1_stage_f32_L64M(kc, grid, a, st);
       default: return hipErrorInvalidValue;  // the 256 x 256 tile is bf16 only
     }
   }
@@ -55,6 +59,7 @@ hipError_t launch_k1(int bf16, int dma, int layout, int kc, dim3 grid, const K1A
       case K1_L32M: return launch_k1_dma_L32M(kc, grid, a, st);
       case K1_L32S: return launch_k1_dma_L32S(kc, grid, a, st);
       case K1_L64: return launch_k1_dma_L64(kc, grid, a, st);
+      case K1_L64M: return launch_k1_dma_L64M(kc, grid, a, st);
       default: return launch_k1_dma_L32(kc, grid, a, st);
     }
   }
@@ -64,6 +69,7 @@ hipError_t launch_k1(int bf16, int dma, int layout, int kc, dim3 grid, const K1A
     case K1_L32: return launch_k1_stage_bf16_L32(kc, grid, a, st);
     case K1_L32M: return launch_k1_stage_bf16_L32M(kc, grid, a, st);
     case K1_L32S: return launch_k1_stage_bf16_L32S(kc, grid, a, st);
+    case K1_L64M: return launch_k1_stage_bf16_L64M(kc, grid, a, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -225,7 +231,7 @@ constexpr long long kFewMaxWeightsBf16 = 64ll << 20;
 // KB_TILE=<rows>x<words> (e.g. 32x256) at call time replaces the modelled
 // choice by that tile where the step's path has it (for measuring the cost
 // model; the tuning script sets it): 128x256, 256x128, 32x512, 32x256,
-// 32x128, 64x128 on the DMA pipeline (dma), and 256x256 on the bf16 DMA
+// 32x128, 64x256, 64x128 on the DMA pipeline (dma), and 256x256 on the bf16 DMA
 // pipeline with V >= 256 (wide_ok).  Other values are ignored.
 // A tile wider than V words is one of them on the register-staged kernel (max_words).
 void apply_tile_override(bool dma, bool wide_ok, int max_words, Plan& p) {
@@ -240,6 +246,7 @@ void apply_tile_override(bool dma, bool wide_ok, int max_words, Plan& p) {
   else if (r == 32 && w == 512) layout = kb::K1_L32;
   else if (r == 32 && w == 256) layout = kb::K1_L32M;
   else if (r == 32 && w == 128) layout = kb::K1_L32S;
+  else if (r == 64 && w == 256) layout = kb::K1_L64M;
   else if (r == 64 && w == 128 && dma) layout = kb::K1_L64;
   if (layout < 0 || w > max_words) return;
   p.layout = layout;

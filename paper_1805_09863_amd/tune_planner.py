@@ -41,17 +41,18 @@ from paper_1805_09863_amd.hipevents import HipEvents
 TILES = {  # KB_TILE value -> (rows, words) per tile
     "256x256": (256, 256), "128x256": (128, 256), "256x128": (256, 128),
     "32x512": (32, 512), "32x256": (32, 256), "32x128": (32, 128), "64x128": (64, 128),
+    "64x256": (64, 256),
 }
 GRIDS = {
     "f32": dict(H=(256, 512, 1024, 2048), V=(8000, 30000, 60000),
                 N=(40, 64, 100, 160, 240, 320, 480, 640, 960, 1280),
-                tiles=("128x256", "256x128", "32x512", "32x256", "32x128", "64x128")),
+                tiles=("128x256", "256x128", "32x512", "32x256", "32x128", "64x128", "64x256")),
     "f32reg": dict(H=(264, 520, 1032, 2056), V=(8000, 30000, 60000),
                    N=(40, 64, 100, 160, 240, 320, 480, 640, 960, 1280),
-                   tiles=("128x256", "256x128", "32x512", "32x256", "32x128")),
+                   tiles=("128x256", "256x128", "32x512", "32x256", "32x128", "64x256")),
     "bf16reg": dict(H=(500, 1000, 2000), V=(8001, 30001, 50001, 90001),
                     N=(12, 24, 40, 64, 100, 160, 240, 320, 480, 640, 960, 1280, 2560),
-                    tiles=("128x256", "256x128", "32x512", "32x256", "32x128")),
+                    tiles=("128x256", "256x128", "32x512", "32x256", "32x128", "64x256")),
     "bf16": dict(H=(512, 1024, 2048), V=(8000, 30000, 50000, 90000),
                  N=(40, 64, 100, 160, 240, 320, 480, 640, 960, 1280, 2560),
                  tiles=tuple(TILES)),

@@ -44,7 +44,7 @@ def test_vocabulary_sizes(kb, dt, V):
 
 
 @pytest.mark.parametrize("dt", ["bf16", "f32"])
-@pytest.mark.parametrize("tile", ["128x256", "256x128", "32x512", "32x256", "32x128"])
+@pytest.mark.parametrize("tile", ["128x256", "256x128", "32x512", "32x256", "32x128", "64x256"])
 def test_operands_at_odd_addresses(kb, dt, tile, monkeypatch):
     # h, W and b one element past a 16-byte boundary: shapes that are otherwise
     # 16-byte loadable, and V odd
@@ -91,3 +91,16 @@ def test_float32_split_carries_every_bit(kb):
     # six pieces' products: the three left out are below 2^-22 of the product together, then one float32 rounding each
     assert err.max() < 2.0 ** -21
     assert np.allclose(x[np.arange(N), tok.cpu().numpy()], want, rtol=2.0 ** -20)
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+@pytest.mark.parametrize("H,V", [(128, 5000), (100, 5003)])
+def test_64_row_tile_of_256_words(kb, dt, H, V, monkeypatch):
+    # the DMA pipeline's (aligned bf16) and the register-staged form, over
+    # several row tiles, ragged rows and words, k from 1 to 16
+    monkeypatch.setenv("KB_TILE", "64x256")
+    for k, rps in ((1, [1] * 64), (7, [7] * 21), (12, [12] * 11), (16, [16] * 4 + [1])):
+        inp = wl.make_step(H=H, V=V, k=k, rows_per_sentence=rps, dtype=dt, seed=4600 + k, name=f"64x256 k{k}")
+        plan = kb.kbest_plan(kb.KB_BF16 if dt == "bf16" else kb.KB_F32, inp.N, H, V, k)
+        assert (plan["tile_rows"], plan["tile_words"]) == (64, 256)
+        check(inp, run_step(kb, inp, row_lse=True))
