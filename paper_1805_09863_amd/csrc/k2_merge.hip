@@ -1,10 +1,13 @@
 // K2: merge the vocabulary splits of every row, then the rows of every sentence.
 //
-// One workgroup per sentence, W waves (one per row of an average sentence,
-// W <= 16, and no more than the staged lists fit in LDS); the sentence's rows
-// are taken W at a time, one per wave:
-//   * the row's P split lists are staged in LDS, eight or sixteen loads in
-//     flight per lane, and its P split statistics held in registers;
+// One workgroup per sentence, W waves (one per row of an average sentence, two
+// past 128 splits, W <= 16, and no more than the staged lists fit in LDS); the
+// sentence's rows are taken as many at a time as there are waves.  With two
+// waves a row each takes half of its splits (one wave with four lists a lane
+// spent twice the time of two in the rounds: 8.7 us against 6.9 at 5 rows and
+// 196 splits):
+//   * the row's split lists are staged in LDS, sixteen loads in flight per
+//     lane, while its split statistics are reduced in registers;
 //   * LSE = M + ln(sum_p s_p * exp(m_p - M)) over the P split partials -- the
 //     rescaling identity of Algorithm 4 applied between shards, the reduction
 //     step of Algorithm 6 extended from (max, best) to softmax statistics;
@@ -26,7 +29,7 @@
 namespace kb {
 
 constexpr int K2_MAXW = 16;                  // waves per workgroup: rows merged at once
-constexpr int K2_LPL = 4;                    // split lists per lane: P <= 256
+constexpr int K2_MAXP = 256;                 // splits: up to two lists per lane of two waves
 constexpr int K2_LS = 16;                    // LDS slots per staged split list (k <= 16)
 constexpr int K2_C = K2_MAXW * 16 + 16 + 2;  // running best + one chunk (+ pad to pairs)
 constexpr int kNegInfBits = (int)0xff800000;  // -inf: the score of an empty entry (word INT_MAX)
@@ -71,23 +74,26 @@ __device__ __forceinline__ float log_plus(float M, float S) {
 // and flat index: a higher score, then a lower flat index, gives the larger key.
 __device__ __forceinline__ uint64_t cand_key(float score, int flat) { return key_of(score, flat); }
 
-// NQ: split lists per lane (P <= 64 * NQ); MAXT: the workgroup size it is
-// compiled for (1024: up to 16 waves, 128 VGPRs; 512: up to 8, 256 VGPRs,
-// which lets a lane keep a whole row's staging loads in flight)
-template <int NQ, int MAXT>
-__global__ __launch_bounds__(MAXT) void k2_merge(K2Args a) {
+// NQ: split lists per lane (at most 64 * NQ per wave); HW: waves per row.  Up
+// to 16 waves, so 128 VGPRs: a form for 8 waves and 256 VGPRs staged longer
+// lists in one batch, but two waves a row do so too, without its spilled SGPRs.
+template <int NQ, int HW>
+__global__ __launch_bounds__(64 * K2_MAXW) void k2_merge(K2Args a) {
   __shared__ __align__(16) uint64_t key[K2_C];  // read two at a time when ranked
   __shared__ int c_t[K2_C];
   __shared__ int c_p[K2_C];
   __shared__ uint64_t n_key[16];
   __shared__ int n_t[16], n_p[16];
+  __shared__ float2 half_st[K2_MAXW];  // each wave's (max, sum) of its share of a row's splits
   // one list of empty entries, then per wave one row's P lists of K2_LS slots
   extern __shared__ int2 lists_dyn[];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int W = blockDim.x >> 6;
+  const int RW = (blockDim.x >> 6) / HW;  // rows at a time
   const int s = blockIdx.x;
-  const int k = a.k, P = a.P;
+  const int k = a.k;
+  // this wave's splits p_lo .. p_lo + P - 1
+  const int share = (a.P + HW - 1) / HW, p_lo = (wave % HW) * share, P = min(share, a.P - p_lo);
   const int r0 = a.off[s], r1 = a.off[s + 1];
 
   if (tid < K2_LS) lists_dyn[tid] = make_int2(kNegInfBits, INT_MAX);
@@ -98,7 +104,7 @@ __global__ __launch_bounds__(MAXT) void k2_merge(K2Args a) {
     c_t[tid] = -1;
     c_p[tid] = -1;
   }
-  const int wbase = K2_LS + wave * P * K2_LS;  // this wave's lists in lists_dyn
+  const int wbase = K2_LS + wave * share * K2_LS;  // this wave's lists in lists_dyn
   int lidx[NQ];  // each lane's lists, or the empty list where it has none
 #pragma unroll
   for (int q = 0; q < NQ; ++q) {
@@ -106,9 +112,9 @@ __global__ __launch_bounds__(MAXT) void k2_merge(K2Args a) {
     lidx[q] = p < P ? wbase + p * K2_LS : 0;
   }
 
-  for (int cr0 = r0; cr0 < r1; cr0 += W) {
-    const int nrows = min(W, r1 - cr0);
-    const int ri = wave;
+  for (int cr0 = r0; cr0 < r1; cr0 += RW) {
+    const int nrows = min(RW, r1 - cr0);
+    const int ri = wave / HW;
     const bool active = ri < nrows;
     const int r = cr0 + ri;
     float2 st[NQ];
@@ -120,18 +126,16 @@ __global__ __launch_bounds__(MAXT) void k2_merge(K2Args a) {
 #pragma unroll
       for (int q = 0; q < NQ; ++q) {
         const int p = lane + 64 * q;
-        st[q] = p < P ? a.stats[(size_t)p * a.N + r] : make_float2(kStatInit, 0.f);
+        st[q] = p < P ? a.stats[(size_t)(p_lo + p) * a.N + r] : make_float2(kStatInit, 0.f);
       }
       prev_r = a.prev[r];
       // lane = kp * g + j (kp: k rounded up to a power of two) stages entry j
       // of lists p0 + g, p0 + gpl + g, ... (gpl = 64 / kp lists per load;
       // slots k .. kp - 1 get empty entries): LB loads in flight per lane
-      // before the first LDS write (as many as the registers allow: 32 in the
-      // 512-thread form, whose row of up to 256 splits then takes one batch
-      // up to k = 8; 16, or 8 for the longest split counts, in the 1024-thread
-      // form).  Slots past kp are never read before a list has given up all
-      // k entries, so they stay unwritten.
-      constexpr int LB = MAXT <= 512 ? 32 : (NQ <= 2 ? 16 : 8);
+      // before the first LDS write, as many as the registers allow.  Slots past
+      // kp are never read before a list has given up all k entries, so they
+      // stay unwritten.
+      constexpr int LB = 16;
       const int lgk = k <= 1 ? 0 : (k <= 2 ? 1 : (k <= 4 ? 2 : (k <= 8 ? 3 : 4)));
       const int j = lane & ((1 << lgk) - 1), g = lane >> lgk, gpl = 64 >> lgk;
       for (int p0 = 0; p0 < P; p0 += LB * gpl) {
@@ -140,7 +144,7 @@ __global__ __launch_bounds__(MAXT) void k2_merge(K2Args a) {
         for (int u = 0; u < LB; ++u) {
           const int p = p0 + u * gpl + g;
           v[u] = make_int2(kNegInfBits, INT_MAX);
-          if (p < P && j < k) v[u] = a.lists[((size_t)p * a.N + r) * k + j];
+          if (p < P && j < k) v[u] = a.lists[((size_t)(p_lo + p) * a.N + r) * k + j];
         }
 #pragma unroll
         for (int u = 0; u < LB; ++u) {
@@ -149,20 +153,28 @@ __global__ __launch_bounds__(MAXT) void k2_merge(K2Args a) {
         }
       }
     }
-    __syncthreads();  // the staged lists are visible; the running best is settled
-    uint64_t my_key = cand_key(-INFINITY, INT_MAX - (k + ri * k + lane));
-    int my_t = -1;
+    float M = kStatInit, S = 0.f;
     if (active) {
-      float M = kStatInit;
 #pragma unroll
       for (int q = 0; q < NQ; ++q) M = fmaxf(M, st[q].x);
       M = wave_max(M);
-      float S = 0.f;
 #pragma unroll
       for (int q = 0; q < NQ; ++q) S += st[q].y * __expf(st[q].x - M);
       S = wave_sum(S);
+      if (HW > 1 && lane == 0) half_st[wave] = make_float2(M, S);
+    }
+    __syncthreads();  // the staged lists are visible; the running best is settled
+    uint64_t my_key = cand_key(-INFINITY, INT_MAX - (k + wave * k + lane));
+    int my_t = -1;
+    if (active) {
+      if constexpr (HW > 1) {
+        const float2 o = half_st[wave ^ 1];
+        const float m = fmaxf(M, o.x);
+        S = S * __expf(M - m) + o.y * __expf(o.x - m);
+        M = m;
+      }
       const float lse = log_plus(M, S);
-      if (a.row_lse != nullptr && lane == 0) a.row_lse[r] = lse;
+      if (a.row_lse != nullptr && lane == 0 && wave % HW == 0) a.row_lse[r] = lse;
       const float base = prev_r - lse;
       const float kth = key_score(key[k - 1]);  // running k-th best (-inf before the first chunk)
 
@@ -207,9 +219,9 @@ __global__ __launch_bounds__(MAXT) void k2_merge(K2Args a) {
         }
       }
     }
-    const int C = k + nrows * k;
+    const int C = k + nrows * HW * k;
     if (active && lane < k) {
-      const int slot = k + ri * k + lane;
+      const int slot = k + wave * k + lane;
       key[slot] = my_key;
       c_t[slot] = my_t;
       c_p[slot] = r;
@@ -288,47 +300,27 @@ hipError_t launch_k2_argmax(const int2* lists, int P, int N, int32_t* tok, float
   return hipGetLastError();
 }
 
-template <int NQ, int MAXT>
-static hipError_t launch_k2_w(const K2Args& a, int W, size_t lds, hipStream_t st) {
+template <int NQ, int HW>
+static hipError_t launch_k2_nq(const K2Args& a, hipStream_t st) {
+  // HW waves per row of a sentence of average length (longer sentences take
+  // their rows in chunks), as many as the staged lists fit in 144 KB of LDS
+  // (the kernel's static LDS is under 5 KB): at most 16 up to P = 72, 8 (4 rows) at P = 256
+  const int share = (a.P + HW - 1) / HW;
+  const size_t per_wave = (size_t)share * K2_LS * sizeof(int2);
+  const int rows_per = (a.N + a.S - 1) / a.S;
+  const int fit = (int)std::min<size_t>(K2_MAXW, (144 * 1024) / per_wave) / HW;  // rows at once
+  const int W = std::min(fit, std::max(1, rows_per)) * HW;
+  const size_t lds = (size_t)K2_LS * sizeof(int2) + (size_t)W * per_wave;
   static bool attr_set = false;  // the kernel's LDS ceiling (at most 144 KB + one list), raised once per process
   if (lds > 48 * 1024 && !attr_set) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k2_merge<NQ, MAXT>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k2_merge<NQ, HW>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize,
                                              (int)(K2_LS * sizeof(int2) + 144 * 1024));
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  k2_merge<NQ, MAXT><<<dim3(a.S), dim3(64 * W), lds, st>>>(a);
+  k2_merge<NQ, HW><<<dim3(a.S), dim3(64 * W), lds, st>>>(a);
   return hipGetLastError();
-}
-
-template <int NQ>
-static hipError_t launch_k2_nq(const K2Args& a, hipStream_t st) {
-  // one wave per row of a sentence of average length (longer sentences take
-  // their rows in chunks), as many as the staged lists fit in 144 KB of LDS
-  // (the kernel's static LDS is under 4 KB): at most 16 up to P = 72, 4 at P = 256
-  const size_t per_wave = (size_t)a.P * K2_LS * sizeof(int2);
-  const int rows_per = (a.N + a.S - 1) / a.S;
-  const int W = (int)std::min<size_t>(std::min(K2_MAXW, std::max(1, rows_per)), (144 * 1024) / per_wave);
-  const size_t lds = (size_t)K2_LS * sizeof(int2) + (size_t)W * per_wave;
-  // past 128 splits a row's lists take more than 16 KB, so at most 8 waves fit:
-  // only the 512-thread form is built for 3 and 4 lists per lane
-  if constexpr (NQ >= 3) {
-    return launch_k2_w<NQ, 512>(a, W, lds, st);
-  } else {
-    // The 512-thread form stages a row's lists in batches of 32 loads per
-    // lane against 16, but takes about 210 VGPRs against 125: a CU then holds
-    // one workgroup of five waves instead of three.  It is used only where it
-    // saves a staging batch (a row's lists past 16 * 64 / kp splits, kp = k
-    // rounded up to a power of two) and the sentences need at most one
-    // workgroup per CU; with more (512 sentences at 25 splits, say) the
-    // 1024-thread form's occupancy halves the merge's time.
-    const int kp = a.k <= 1 ? 1 : (a.k <= 2 ? 2 : (a.k <= 4 ? 4 : (a.k <= 8 ? 8 : 16)));
-    const int per_batch = 16 * (64 / kp);  // lists of a row per batch of the 1024-thread form
-    const bool saves_batch = (a.P + per_batch - 1) / per_batch > (a.P + 2 * per_batch - 1) / (2 * per_batch);
-    return W <= 8 && saves_batch && a.S <= 256 ? launch_k2_w<NQ, 512>(a, W, lds, st)
-                                               : launch_k2_w<NQ, 1024>(a, W, lds, st);
-  }
 }
 
 // A vocabulary shard's partial lists hold shard-local words; this moves them
@@ -349,14 +341,14 @@ hipError_t launch_add_word_base(int2* lists, size_t n, int base, int v_shard, hi
 }
 
 hipError_t launch_k2(const K2Args& a, hipStream_t st) {
-  if (a.P < 1 || a.P > 64 * K2_LPL || a.k < 1 || a.k > K2_LS) return hipErrorInvalidValue;
+  if (a.P < 1 || a.P > K2_MAXP || a.k < 1 || a.k > K2_LS) return hipErrorInvalidValue;
   if (a.S <= 0) return hipSuccess;
-  switch ((a.P + 63) / 64) {
-    case 1: return launch_k2_nq<1>(a, st);
-    case 2: return launch_k2_nq<2>(a, st);
-    case 3: return launch_k2_nq<3>(a, st);
-    default: return launch_k2_nq<4>(a, st);
-  }
+  // two waves a row past 128 splits, and for lists of more than 8 past 64 (a
+  // wave's lists then take one staging batch) where a sentence's rows still
+  // fit in one go
+  if (a.P > 128) return launch_k2_nq<2, 2>(a, st);
+  if (a.P > 64) return a.k > 8 && a.N <= 8 * a.S ? launch_k2_nq<1, 2>(a, st) : launch_k2_nq<2, 1>(a, st);
+  return launch_k2_nq<1, 1>(a, st);
 }
 
 }  // namespace kb
