@@ -12,8 +12,8 @@
 //     (GUARD: the form for H below a stage, V below a tile or beyond 2^25,
 //     which loads element by element);
 //   * a stage in LDS is GROUPS groups of 16 states.  bf16: 32 states, two
-//     groups.  float32: 16 states, three groups, the pieces of the split
-//     below.  W keeps its V-contiguous rows (16-byte chunks XOR-swizzled by
+//     groups.  float32: 16 states (the smallest tile 32), three groups for
+//     each 16, the pieces of the split below.  W keeps its V-contiguous rows (16-byte chunks XOR-swizzled by
 //     the row, fragments through the transpose read ds_read_b64_tr_b16); an h
 //     row holds its groups side by side, padded so that 16 rows' fragments
 //     fall on distinct banks;
@@ -51,27 +51,23 @@ template <>
 struct StageTy<false> {
   using E = uint16_t;
   typedef stage16 V16 __attribute__((aligned(2)));  // 16 bytes at any element
-  static constexpr int BK = 32, EPC = 8, GROUPS = 2, PRODS = 2;
-  static constexpr int HS = 40;   // elements of an h row in LDS: 2 x 16, padded to 80 bytes
+  static constexpr int EPC = 8, PIECES = 1, PRODS = 1;
 };
 template <>
 struct StageTy<true> {
   using E = float;
   typedef stage16 V16 __attribute__((aligned(4)));
-  static constexpr int BK = 16, EPC = 4, GROUPS = 3, PRODS = 6;
-  static constexpr int HS = 48;   // 3 x 16 elements, 96 bytes: no two of 16 rows share a bank
+  static constexpr int EPC = 4, PIECES = 3, PRODS = 6;
 };
 
-// (W group, h group) of product p
-template <bool F32>
+// (W piece, h piece) of product p
 __device__ constexpr int prod_w(int p) {
   constexpr int w[6] = {2, 0, 1, 1, 0, 0};
-  return F32 ? w[p] : p;
+  return w[p];
 }
-template <bool F32>
 __device__ constexpr int prod_h(int p) {
   constexpr int h[6] = {0, 2, 1, 0, 1, 0};
-  return F32 ? h[p] : p;
+  return h[p];
 }
 
 // The three bf16 pieces of two floats, each pair packed, in two parts of five
@@ -90,22 +86,34 @@ __device__ __forceinline__ void split_rest(f32x2 r, uint32_t& p1, uint32_t& p2) 
 template <class L, bool F32>
 struct StageGeom {
   using T = StageTy<F32>;
+  // blocks of 16 states per stage: two, or one of float32, whose three pieces
+  // fill LDS and registers otherwise; the smallest float32 tile, whose stages
+  // are little but barrier and latency, takes two (12 rows, H = 1024,
+  // V = 11,280: 37 -> 30 us; the next larger tile lost 3%, bf16's smallest
+  // spilled)
+  static constexpr int KS = F32 && !(L::BH == 32 && L::BV == 128) ? 1 : 2;
+  static constexpr int BK = 16 * KS, GROUPS = KS * T::PIECES;
+  // elements of an h row in LDS: its groups, padded so that the rows a read
+  // takes at once (8 of 16 bytes) fall on distinct banks
+  static constexpr int HS = F32 ? (KS == 1 ? 48 : 112) : 40;
+  static constexpr int CPR = BK / T::EPC;               // chunks of a stage per h row
   static constexpr int WCH = L::BV / T::EPC;            // 16-byte chunks per W row
-  static constexpr int W_OPS = T::BK * WCH / 256;       // chunks of W per thread and stage
-  static constexpr int H_SLOTS = L::BH * 4;             // an h row is four chunks
+  static constexpr int W_OPS = BK * WCH / 256;          // chunks of W per thread and stage
+  static constexpr int H_SLOTS = L::BH * CPR;
   static constexpr int H_OPS = (H_SLOTS + 255) / 256;
   static constexpr int OPS = W_OPS + H_OPS;
   // Register sets, i.e. stages between a load and its use, which have to cover
   // a memory round trip (about 1.2 us): 2 for float32 tiles of 128 rows and
-  // more (1,536 cycles of products a stage), else 4, or 8 for the tiles of
-  // few products a stage where the registers allow.
-  static constexpr int NSET = F32 ? (L::BH >= 128 ? 2 : (OPS <= 3 && L::BH == 32 ? 8 : 4)) : (OPS <= 5 ? 8 : 4);
+  // more (1,536 cycles of products a stage), else 4, or 8 for the bf16 tiles
+  // of few products a stage.
+  static constexpr int NSET = F32 ? (L::BH >= 128 ? 2 : 4) : (OPS <= 5 ? 8 : 4);
   static constexpr int WG = 16 * L::BV;                 // elements of a W group
-  static constexpr int WE = T::GROUPS * WG, HE = L::BH * T::HS;
-  static_assert(T::BK * WCH % 256 == 0, "whole chunks per thread");
+  static constexpr int WE = GROUPS * WG, HE = L::BH * HS;
+  static_assert(BK * WCH % 256 == 0, "whole chunks per thread");
   // (32 rows: two threads load, split and write the same chunk, which costs
   // less than a branch)
   static_assert(H_SLOTS % 256 == 0 || H_SLOTS == 128, "whole waves load h");
+  static_assert(256 % CPR == 0, "a thread's chunks are of the same states");
   static_assert(L::BV / 8 >= 16, "the swizzle permutes 16 chunks");
 };
 
@@ -124,7 +132,7 @@ void k1_stage(K1Args a) {
   using E = typename T::E;
   using GP = const KB_GLOBAL E*;
   constexpr int BV = L::BV, BH = L::BH, WV = L::WV, WH = L::WH, NWV = L::NWV;
-  constexpr int BK = T::BK, EPC = T::EPC, GROUPS = T::GROUPS, NSET = G::NSET, HS = T::HS;
+  constexpr int BK = G::BK, EPC = T::EPC, PIECES = T::PIECES, GROUPS = G::GROUPS, NSET = G::NSET, HS = G::HS;
   constexpr int ESZ = sizeof(E);
   __shared__ __attribute__((aligned(16))) uint16_t S[2][G::WE + G::HE];
   __shared__ __attribute__((aligned(16))) SmemEpi<L, KC> ep;
@@ -145,12 +153,12 @@ void k1_stage(K1Args a) {
   epi.init(ep, a.k);
 
   // ---- loads: chunk i of this thread is W row wr(i), words wc(i).., or, past
-  // the W chunks, states kc.. of h row (tid + 256 i) / 4.  Byte offsets from
+  // the W chunks, states kc.. of h row hslot(i).  Byte offsets from
   // the stage's first W row and h column, which are uniform.
   auto wr = [&](int i) { return (tid + 256 * i) / G::WCH; };
   auto wc = [&](int i) { return (tid + 256 * i) % G::WCH * EPC; };
-  const int kc = (tid & 3) * EPC;
-  auto hslot = [&](int i) { return (tid + 256 * i) % G::H_SLOTS >> 2; };
+  const int kc = (tid % G::CPR) * EPC;
+  auto hslot = [&](int i) { return (tid + 256 * i) % G::H_SLOTS / G::CPR; };
   auto hrow = [&](int i) { return min(h0 + hslot(i), a.N - 1); };  // rows >= N: never written
   const KB_GLOBAL char* const Wg = (const KB_GLOBAL char*)(const KB_GLOBAL void*)a.W;
   const KB_GLOBAL char* const Hg = (const KB_GLOBAL char*)(const KB_GLOBAL void*)a.h;
@@ -242,14 +250,14 @@ void k1_stage(K1Args a) {
     int at;
     if (w) {
       const int rr = wr(i), c = wc(i);
-      at = rr * BV + (((c >> 3) ^ wswz(rr)) << 3) + (c & 7);
+      at = rr / 16 * PIECES * G::WG + rr % 16 * BV + (((c >> 3) ^ wswz(rr)) << 3) + (c & 7);
     } else {
-      at = G::WE + hslot(i - G::W_OPS) * HS + kc;
+      at = G::WE + hslot(i - G::W_OPS) * HS + kc / 16 * PIECES * 16 + kc % 16;
     }
     if constexpr (F32) {
       const int gs = w ? G::WG : 16;
 #pragma unroll
-      for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x2*>(buf + at + p * gs) = u32x2{piece[p][0], piece[p][1]};
+      for (int p = 0; p < PIECES; ++p) *reinterpret_cast<u32x2*>(buf + at + p * gs) = u32x2{piece[p][0], piece[p][1]};
     } else {
       *reinterpret_cast<stage16*>(buf + at) = r[i];
     }
@@ -283,10 +291,10 @@ void k1_stage(K1Args a) {
   };
 
   f32x16 acc[WV][WH];
-  constexpr int NB = WV * WH, M = T::PRODS * NB;  // products of a stage
+  constexpr int NB = WV * WH, M = G::KS * T::PRODS * NB;  // products of a stage
   auto product = [&](const Frag& f, int i) __attribute__((always_inline)) {
-    const int p = i / NB, vb = i % NB / WH, hb = i % NB % WH;
-    const int gw = prod_w<F32>(p), gh = prod_h<F32>(p);
+    const int ks = i / NB / T::PRODS, p = i / NB % T::PRODS, vb = i % NB / WH, hb = i % NB % WH;
+    const int gw = ks * PIECES + (F32 ? prod_w(p) : 0), gh = ks * PIECES + (F32 ? prod_h(p) : 0);
     const bf16x8 fa =
         __builtin_bit_cast(bf16x8, __builtin_shufflevector(f.lo[gw][vb], f.hi[gw][vb], 0, 1, 2, 3, 4, 5, 6, 7));
     acc[vb][hb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, f.b[gh][hb], acc[vb][hb], 0, 0, 0);
@@ -388,7 +396,7 @@ hipError_t launch_k1_stage_kc(bool guard, dim3 grid, const K1Args& a, hipStream_
 
 template <class L, bool F32>
 hipError_t launch_k1_stage(int kc, dim3 grid, const K1Args& a, hipStream_t st) {
-  const bool guard = stage_guarded(F32, a.H, a.V);
+  const bool guard = stage_guarded(a.H, a.V);
   if (!guard && a.V < L::BV) return hipErrorInvalidValue;
   switch (kc) {
     case 4: return launch_k1_stage_kc<L, 4, F32>(guard, grid, a, st);

@@ -101,7 +101,7 @@ enum K1Layout { K1_L256 = 0, K1_L128 = 1, K1_L32 = 2, K1_W256 = 3, K1_L32M = 4, 
 // layout K1_W256 (256 x 256 tiles) exists only with it.  Everything else is staged
 // through registers (k1_stage.hpp), whose tiles are no wider than the vocabulary.
 // stage_guarded: the shapes that kernel takes element by element, with 32 x 128 tiles.
-inline bool stage_guarded(bool f32, int H, int V) { return H < (f32 ? 16 : 32) || V < 128 || V > (1 << 25); }
+inline bool stage_guarded(int H, int V) { return H < 32 || V < 128 || V > (1 << 25); }
 hipError_t launch_k1(int bf16, int dma, int layout, int kc, dim3 grid, const K1Args& a, hipStream_t st);
 hipError_t launch_zero_u32(uint32_t* p, int n, hipStream_t st);
 

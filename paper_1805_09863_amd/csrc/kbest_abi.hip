@@ -274,7 +274,7 @@ Plan make_plan(int dtype, int N, int H, int V, int k, bool dma, bool vec) {
   Plan p{};
   const bool dma_path = dma && dma_shape(dtype, H, V);
   const bool staged = dtype == KB_F32 || !dma_path;  // the register-staged kernel, few rows aside
-  const bool guarded = staged && kb::stage_guarded(dtype == KB_F32, H, V);
+  const bool guarded = staged && kb::stage_guarded(H, V);
   const int few_cw = kb::few_chunk_words(dtype == KB_BF16);
   const int few_nt = (V + few_cw - 1) / few_cw, few_p = std::min(few_nt, kTargetCUs);
   const long long few_work = (long long)N * H * V, few_weights = (long long)H * V;
