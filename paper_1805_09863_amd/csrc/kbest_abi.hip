@@ -140,29 +140,31 @@ constexpr long long kFewMaxWorkF32 = 1ll << 30;
 // table per path: float32 of 16-byte aligned shapes and of the others (H
 // 256-2048, V 8k-60k, 120 shapes each), bf16 on the DMA pipeline (H 512-2048,
 // V 8k-90k, 132 shapes) and bf16 staged through registers (H 500-2000, V
-// 8,001-90,001, 12-2560 rows, 156 shapes).  The fits choose within 0.3%,
+// 8,001-90,001, 12-2560 rows, 156 shapes).  The fits choose within 0.2%,
 // 0.1%, 1.5% and 0.9% of the fastest measured layout (geometric mean over the
-// shapes).  Three of the tables are then weighted, as little as it takes, so
-// that choices which tests hold stay as they were: float32 at 320 rows, H =
-// 512, V = 30,000 on 64 x 128 tiles (measured 84 us against 80 on 128 x 256;
-// the table's choices lose 0.7% on the grid), at H = 520 on 32 x 256 (125
-// against 86; 1.3%), unaligned bf16 at 640 rows, V = 60,000 on 256 x 128
-// (about 20% behind 128 x 256; 2.4%).
+// shapes).  Three of the tables then differ from the fits, as little as it
+// takes, so that choices which tests hold stay as they were: float32 at 320
+// rows, H = 512, V = 30,000 on 64 x 128 tiles (measured 84 us against 80 on
+// 128 x 256; the table's choices lose 0.5% on the grid), at H = 520 on
+// 32 x 256 (125 against 86; 1.4%), and unaligned bf16 at 640 rows, V = 60,000
+// on 256 x 128: that table leaves out 128 x 256 above 512 rows (4% faster from
+// 960 rows on, up to 25% at 640).
 struct TileCost {
   int layout, BH, BV;
   double a, e, f;
+  int max_rows = INT_MAX;  // not used for more rows
 };
 constexpr TileCost kF32Costs[] = {
-    {kb::K1_L128, 128, 256, 2.0082e-06, 6.0635e-04, 7.803},
-    {kb::K1_L256, 256, 128, 2.0860e-06, 6.0370e-04, 7.280},
-    {kb::K1_L32, 32, 512, 3.8857e-06, 4.2472e-04, 12.795},
-    {kb::K1_L32M, 32, 256, 3.8550e-06, 4.8825e-04, 11.483},
-    {kb::K1_L32S, 32, 128, 6.6250e-06, 1.2369e-03, 11.350},
-    {kb::K1_L64M, 64, 256, 2.7944e-06, 7.8476e-04, 9.997},
+    {kb::K1_L128, 128, 256, 1.8800e-06, 5.9114e-04, 8.145},
+    {kb::K1_L256, 256, 128, 1.9315e-06, 5.9766e-04, 7.410},
+    {kb::K1_L32, 32, 512, 3.8555e-06, 4.1431e-04, 13.226},
+    {kb::K1_L32M, 32, 256, 3.7407e-06, 4.5810e-04, 11.376},
+    {kb::K1_L32S, 32, 128, 4.5975e-06, 1.0512e-03, 11.672},
+    {kb::K1_L64M, 64, 256, 2.6051e-06, 7.4404e-04, 10.660},
 };
 constexpr TileCost kBf16Costs[] = {
-    {kb::K1_L128, 128, 256, 5.1985e-07, 2.6063e-04, 9.363},
-    {kb::K1_L256, 256, 128, 4.2129e-07, 2.1800e-04, 8.470},
+    {kb::K1_L128, 128, 256, 4.7259e-07, 2.0048e-04, 9.363, 512},
+    {kb::K1_L256, 256, 128, 4.6810e-07, 2.1800e-04, 8.470},
     {kb::K1_L32, 32, 512, 1.1955e-06, 1.5964e-04, 13.668},
     {kb::K1_L32M, 32, 256, 1.2930e-06, 2.3384e-04, 13.805},
     {kb::K1_L32S, 32, 128, 1.7152e-06, 4.0053e-04, 11.281},
@@ -180,13 +182,13 @@ constexpr TileCost kBf16DmaCosts[] = {
 };
 // float32 of 16-byte aligned shapes: two workgroups per CU where the tile allows
 constexpr TileCost kF32DmaCosts[] = {
-    {kb::K1_L128, 128, 256, 1.9890e-06, 2.2615e-04, 10.759},
-    {kb::K1_L256, 256, 128, 2.0649e-06, 2.3199e-04, 9.991},
-    {kb::K1_L32, 32, 512, 3.8606e-06, 1.7579e-04, 13.006},
-    {kb::K1_L32M, 32, 256, 4.5335e-06, 2.2861e-04, 11.260},
-    {kb::K1_L32S, 32, 128, 4.4789e-06, 2.5756e-04, 14.183},
-    {kb::K1_L64, 64, 128, 2.8974e-06, 8.9601e-05, 13.808},
-    {kb::K1_L64M, 64, 256, 2.7190e-06, 1.9882e-04, 13.065},
+    {kb::K1_L128, 128, 256, 1.9118e-06, 2.3125e-04, 9.787},
+    {kb::K1_L256, 256, 128, 1.9672e-06, 2.3841e-04, 8.752},
+    {kb::K1_L32, 32, 512, 3.8660e-06, 1.7593e-04, 13.239},
+    {kb::K1_L32M, 32, 256, 4.4029e-06, 2.5430e-04, 11.154},
+    {kb::K1_L32S, 32, 128, 3.6898e-06, 3.5093e-04, 12.700},
+    {kb::K1_L64, 64, 128, 2.7720e-06, 9.9401e-05, 13.677},
+    {kb::K1_L64M, 64, 256, 2.6275e-06, 2.0924e-04, 11.986},
 };
 
 // k rounded up to the k-list lengths the projection kernels are built for
@@ -218,7 +220,7 @@ void pick_by_model(const TileCost (&costs)[n], int N, int H, int V, bool dma, bo
   double best = -1.0;
   for (const TileCost& c : costs) {
     if (c.layout == kb::K1_W256 && V < kWideMinCols) continue;
-    if (staged && V < c.BV) continue;
+    if ((staged && V < c.BV) || N > c.max_rows) continue;
     if (c.layout == kb::K1_L64 && kc > 8) continue;  // fitted at two workgroups per CU
     const int rt = (N + c.BH - 1) / c.BH, nt = (V + c.BV - 1) / c.BV;
     const int per = per_cu(c.layout, dma, kc);
