@@ -31,6 +31,7 @@ namespace kb {
 constexpr int K2_MAXW = 16;                  // waves per workgroup: rows merged at once
 constexpr int K2_MAXP = 256;                 // splits: up to two lists per lane of two waves
 constexpr int K2_LS = 16;                    // LDS slots per staged split list (k <= 16)
+constexpr int K2_PAD = 2;                    // slots after the last list: a spent list's next entry is read, never used
 constexpr int K2_C = K2_MAXW * 16 + 16 + 2;  // running best + one chunk (+ pad to pairs)
 constexpr int kNegInfBits = (int)0xff800000;  // -inf: the score of an empty entry (word INT_MAX)
 static_assert(K2_C % 2 == 0, "candidate keys are read in pairs");
@@ -178,45 +179,77 @@ __global__ __launch_bounds__(64 * K2_MAXW) void k2_merge(K2Args a) {
       const float base = prev_r - lse;
       const float kth = key_score(key[k - 1]);  // running k-th best (-inf before the first chunk)
 
-      // per list of this lane: the key of its head (entry ptr) and the entry after it
-      uint64_t hk[NQ];
+      // per list of this lane: its head's key in two halves, and the entry after it
+      uint32_t hi[NQ], lo[NQ];
       int2 nx[NQ];
-      int ptr[NQ];
+      int at[NQ];
 #pragma unroll
       for (int q = 0; q < NQ; ++q) {
         const int2 h = lists_dyn[lidx[q]];
-        nx[q] = lists_dyn[lidx[q] + 1];
-        hk[q] = key_of(__int_as_float(h.x), h.y);
-        ptr[q] = 0;
+        at[q] = lidx[q] + 1;
+        nx[q] = lists_dyn[at[q]];
+        const uint64_t hk = key_of(__int_as_float(h.x), h.y);
+        hi[q] = (uint32_t)(hk >> 32);
+        lo[q] = (uint32_t)hk;
       }
+      // A round is one chain of dependent instructions, some 8 cycles each, so
+      // it has as few as there can be: one maximum over the high words (the low
+      // ones only where two heads share it), the winner out of its lane as two
+      // scalars, no branch but that and the cut-off.
+      uint32_t my_hi = (uint32_t)(kEmptyKey >> 32), my_lo = (uint32_t)kEmptyKey;  // lane jr: the row's jr-th best
       for (int jr = 0; jr < k; ++jr) {
-        // the wave-wide best head (branch-free: DPP and scalar maxima on keys)
-        uint64_t best = hk[0];
+        uint32_t m = hi[0];
 #pragma unroll
-        for (int q = 1; q < NQ; ++q) best = hk[q] > best ? hk[q] : best;
-        const uint64_t win = wave_max64(best);
-        const float wv = key_score(win);
-        const int wi = key_index(win);
-        // the row's later entries are worse still: once this one scores below
-        // the sentence's k-th best of the rows ranked so far, none can enter
-        if (wv + base < kth) break;
-        if (lane == jr && wv > -INFINITY) {
-          my_key = cand_key(wv + base, (r - r0) * a.V + wi);
-          my_t = wi;
-        }
-        // the list whose head won advances (words are unique; empty heads
-        // are all alike and advance together); every lane then reloads the
-        // entry after its heads, so the read is waited for only at the next
-        // advance.  A list advances at most once a round, k rounds in all,
-        // and its head is compared only while rounds remain, so the clamped
-        // read past the last slot is never used.
+        for (int q = 1; q < NQ; ++q) m = max(m, hi[q]);
+        const uint32_t top = wave_umax(m);
+        uint64_t won[NQ];  // the lanes whose head it is
+        int heads = 0;
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
-          const bool adv = hk[q] == win;
-          hk[q] = adv ? key_of(__int_as_float(nx[q].x), nx[q].y) : hk[q];
-          ptr[q] += adv ? 1 : 0;
-          nx[q] = lists_dyn[lidx[q] + min(ptr[q] + 1, K2_LS - 1)];
+          won[q] = __ballot(hi[q] == top);
+          heads += __builtin_popcountll(won[q]);
         }
+        uint32_t low;
+        if (heads == 1) {
+          low = __builtin_amdgcn_readlane((int)lo[0], __builtin_ctzll(won[0]) & 63);
+#pragma unroll
+          for (int q = 1; q < NQ; ++q) {
+            const uint32_t l = __builtin_amdgcn_readlane((int)lo[q], __builtin_ctzll(won[q]) & 63);
+            low = won[q] != 0 ? l : low;
+          }
+        } else {
+          // equal scores: the lowest word (empty heads are all alike and advance together)
+          uint32_t l = 0;
+#pragma unroll
+          for (int q = 0; q < NQ; ++q) l = max(l, hi[q] == top ? lo[q] : 0u);
+          low = wave_umax(l);
+#pragma unroll
+          for (int q = 0; q < NQ; ++q) won[q] = __ballot(hi[q] == top && lo[q] == low);
+        }
+        // the row's later entries are worse still: once this one scores below
+        // the sentence's k-th best of the rows ranked so far, none can enter
+        if (cr0 != r0 && key_score((uint64_t)top << 32) + base < kth) break;
+        my_hi = lane == jr ? top : my_hi;
+        my_lo = lane == jr ? low : my_lo;
+        // The list whose head won advances; every lane then reloads the
+        // entry after its heads, so the read is waited for only at the next
+        // round.  A list advances at most once a round, k rounds in all, and
+        // its head is compared only while rounds remain, so what is read past
+        // its k entries (within the staged lists and their pad) is never used.
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+          const bool adv = __builtin_amdgcn_inverse_ballot_w64(won[q]);
+          const uint64_t nk = key_of(__int_as_float(nx[q].x), nx[q].y);
+          hi[q] = adv ? (uint32_t)(nk >> 32) : hi[q];
+          lo[q] = adv ? (uint32_t)nk : lo[q];
+          at[q] += adv ? 1 : 0;
+          nx[q] = lists_dyn[at[q]];
+        }
+      }
+      const uint64_t mine = ((uint64_t)my_hi << 32) | my_lo;
+      if (lane < k && key_score(mine) > -INFINITY) {
+        my_t = key_index(mine);
+        my_key = cand_key(key_score(mine) + base, (r - r0) * a.V + my_t);
       }
     }
     const int C = k + nrows * HW * k;
@@ -310,12 +343,12 @@ static hipError_t launch_k2_nq(const K2Args& a, hipStream_t st) {
   const int rows_per = (a.N + a.S - 1) / a.S;
   const int fit = (int)std::min<size_t>(K2_MAXW, (144 * 1024) / per_wave) / HW;  // rows at once
   const int W = std::min(fit, std::max(1, rows_per)) * HW;
-  const size_t lds = (size_t)K2_LS * sizeof(int2) + (size_t)W * per_wave;
+  const size_t lds = (size_t)(K2_LS + K2_PAD) * sizeof(int2) + (size_t)W * per_wave;
   static bool attr_set = false;  // the kernel's LDS ceiling (at most 144 KB + one list), raised once per process
   if (lds > 48 * 1024 && !attr_set) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k2_merge<NQ, HW>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             (int)(K2_LS * sizeof(int2) + 144 * 1024));
+                                             (int)((K2_LS + K2_PAD) * sizeof(int2) + 144 * 1024));
     if (e != hipSuccess) return e;
     attr_set = true;
   }

@@ -37,27 +37,39 @@ __device__ __forceinline__ uint64_t readlane64(uint64_t v, int l) {
 // DPP lane patterns within a row of 16 lanes: quad xor 1, quad xor 2,
 // half-row mirror, row mirror (every lane has a source in each)
 constexpr int kDppQXor1 = 0xB1, kDppQXor2 = 0x4E, kDppRowHalfMirror = 0x141, kDppRowMirror = 0x140;
-template <int CTRL>
+// ... and row 0's or 2's last lane to the next row, row 1's to rows 2 and 3
+constexpr int kDppBcast15 = 0x142, kDppBcast31 = 0x143;
+template <int CTRL, int ROWS = 0xF>
 __device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
 }
 
-// wave-wide unsigned maximum; 0 is the identity, so the moves need no bound control
+// Wave-wide unsigned maximum, a scalar; 0 is the identity, so the moves need
+// no bound control.  One lane is read out: the four rows' maxima read out and
+// compared on the scalar unit took longer, and left the result in a vector.
 __device__ __forceinline__ uint32_t wave_umax(uint32_t v) {
   v = max(v, dpp_u32<kDppQXor1>(v));
   v = max(v, dpp_u32<kDppQXor2>(v));
   v = max(v, dpp_u32<kDppRowHalfMirror>(v));
   v = max(v, dpp_u32<kDppRowMirror>(v));
-  const uint32_t a0 = __builtin_amdgcn_readlane((int)v, 0), a1 = __builtin_amdgcn_readlane((int)v, 16);
-  const uint32_t a2 = __builtin_amdgcn_readlane((int)v, 32), a3 = __builtin_amdgcn_readlane((int)v, 48);
-  return max(max(a0, a1), max(a2, a3));
+  v = max(v, dpp_u32<kDppBcast15, 0xA>(v));
+  v = max(v, dpp_u32<kDppBcast31, 0xC>(v));
+  return __builtin_amdgcn_readlane((int)v, 63);
 }
 
-// the wave's largest 64-bit key; every lane gets it
+// The wave's largest 64-bit key; every lane gets it.  The low words are
+// compared only where lanes share the largest high word (equal scores): a
+// round of a selection is a chain of dependent moves, and the second maximum
+// was half of it.
 __device__ __forceinline__ uint64_t wave_max64(uint64_t v) {
-  const uint32_t hi = (uint32_t)(v >> 32);
+  const uint32_t hi = (uint32_t)(v >> 32), lo = (uint32_t)v;
   const uint32_t mh = wave_umax(hi);
-  const uint32_t ml = wave_umax(hi == mh ? (uint32_t)v : 0u);
+  const uint64_t top = __ballot(hi == mh);
+  uint32_t ml;
+  if (__builtin_popcountll(top) == 1)
+    ml = __builtin_amdgcn_readlane((int)lo, __builtin_ctzll(top));
+  else
+    ml = wave_umax(hi == mh ? lo : 0u);
   return ((uint64_t)mh << 32) | ml;
 }
 
