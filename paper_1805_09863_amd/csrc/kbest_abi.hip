@@ -122,14 +122,43 @@ bool dma_shape(int dtype, int H, int V) {
 
 // The few-row kernel holds every row's state in LDS next to its partial sums.
 constexpr size_t kFewLdsMax = 160 * 1024;
-// It streams W at 3.5-4 TB/s and adds its arithmetic after the loads, while
-// the matrix-core kernels carry about 20 us of fixed cost per step.  Measured
-// per step, both ways, at 1-8 rows: float32 (H 512-1024, V 30k, up to 234 M
-// row-weight products) it is 25-40% faster everywhere; bf16 it is faster at
-// V=50k, H=1024 up to 4 rows (195 M products; 32-36 against 32-37 us) and
-// slower from 6 rows, at V=90k (from one row: 47 against 41 us) and at
-// H=2048 (W of 88-102 M weights, where its bf16 dot products are the bound).
+// It streams W and adds its arithmetic and a selection per 64 or 128 words
+// after the loads, while the matrix-core kernels select once per 128 or 256
+// words and cost little more for 8 rows than for one.  Where the one passes
+// the other was measured per step, both ways, at H 256-1024 and V 8k-90k.
+// Float32: up to 4 rows the few-row kernel is faster or even everywhere (256 x
+// 50k, 4 rows: 24.0 against 24.9 us; 1024 x 90k: 85.8 against 84.2; one row
+// 76.8 against 82.1); 5 rows and more up to V = 26k (256 x 20k, 5 rows: 19.3
+// against 21.1; 1024 x 30k: 41.8 against 39.5; 1024 x 50k: 61.2 against 53.5).
+// bf16: up to a V that falls with the rows, and below H = 512 up to a W of so
+// many weights (kFewBf16), near where the two cross: 1024 x 24k, 3 rows
+// 18.6 us both ways, 30k 22.9 against 19.8, 16k 16.0 against 17.9; 512 x 16k,
+// 6 rows 18.6 against 18.7, 24k 20.5 against 19.5; 256 x 50k, one row 12.9
+// against 13.2, 4 rows 17.8 against 16.0.
+constexpr int kFewManyF32 = 4;        // float32 rows up to which V doesn't matter
+constexpr int kFewMaxWordsF32 = 26000;
 constexpr long long kFewMaxWorkF32 = 1ll << 30;
+struct FewLimit {
+  int rows, words;
+  long long weights;
+};
+constexpr FewLimit kFewBf16[] = {{2, 27000, 13500000}, {4, 24000, 8600000}, {6, 16500, 7000000}, {8, 7000, 5000000}};
+// Past H = 1024, and for lists of more than 8 (a beam of that many has as few
+// rows only where it has shrunk), where the crossing was not measured again:
+// no more than these products and weights; at H = 2048 and W of 88-102 M
+// weights its bf16 dot products are the bound.
+constexpr long long kFewMaxWorkBf16 = 200ll << 20;
+constexpr long long kFewMaxWeightsBf16 = 64ll << 20;
+
+bool few_is_faster(int dtype, int N, int H, int V, int k) {
+  const long long weights = (long long)H * V, work = N * weights;
+  if (dtype == KB_F32) return work <= kFewMaxWorkF32 && (N <= kFewManyF32 || V <= kFewMaxWordsF32 || k > 8);
+  if (work > kFewMaxWorkBf16 || weights > kFewMaxWeightsBf16) return false;
+  if (k > 8 || H > 1024) return true;
+  for (const FewLimit& l : kFewBf16)
+    if (N <= l.rows) return V <= l.words || weights <= l.weights;
+  return false;
+}
 
 // Tile choice by a cost model.  A step's projection takes about
 //   (a H + e) x (rows x words one workgroup covers) x slots + f  microseconds,
@@ -243,8 +272,6 @@ void pick_by_model(const TileCost (&costs)[n], int N, int H, int V, bool dma, bo
     }
   }
 }
-constexpr long long kFewMaxWorkBf16 = 200ll << 20;
-constexpr long long kFewMaxWeightsBf16 = 64ll << 20;
 
 // KB_TILE=<rows>x<words> (e.g. 32x256) at call time replaces the modelled
 // choice by that tile where the step's path has it (for measuring the cost
@@ -279,10 +306,7 @@ Plan make_plan(int dtype, int N, int H, int V, int k, bool dma, bool vec) {
   const bool guarded = staged && kb::stage_guarded(H, V);
   const int few_cw = kb::few_chunk_words(dtype == KB_BF16);
   const int few_nt = (V + few_cw - 1) / few_cw, few_p = std::min(few_nt, kTargetCUs);
-  const long long few_work = (long long)N * H * V, few_weights = (long long)H * V;
-  const bool few_fits = dtype == KB_BF16 ? (few_work <= kFewMaxWorkBf16 && few_weights <= kFewMaxWeightsBf16)
-                                         : few_work <= kFewMaxWorkF32;
-  if (vec && N <= kb::FEW_ROWS && V >= few_cw && few_fits &&
+  if (vec && N <= kb::FEW_ROWS && V >= few_cw && few_is_faster(dtype, N, H, V, k) &&
       kb::few_lds_needed(dtype == KB_BF16, N, H, (few_nt + few_p - 1) / few_p) <= kFewLdsMax) {
     // a few rows: one pass over W on the vector ALUs; chunks of few_cw words,
     // as many splits as CUs (at most), each a run of whole chunks
