@@ -13,10 +13,10 @@
 //     which loads element by element);
 //   * a stage in LDS is GROUPS groups of 16 states.  bf16: 32 states, two
 //     groups.  float32: 16 states (the smallest tile 32), three groups for
-//     each 16, the pieces of the split below.  W keeps its V-contiguous rows (16-byte chunks XOR-swizzled by
-//     the row, fragments through the transpose read ds_read_b64_tr_b16); an h
-//     row holds its groups side by side, padded so that 16 rows' fragments
-//     fall on distinct banks;
+//     each 16, the pieces of the split below.  W keeps its V-contiguous rows
+//     (16-byte chunks XOR-swizzled by the row, fragments through the transpose
+//     read ds_read_b64_tr_b16); an h row holds its groups side by side, padded
+//     so that 16 rows' fragments fall on distinct banks;
 //   * two LDS buffers: the fragments of stage g + 1 are read, and stage g + 2
 //     is written to the buffer that stage g left, between the products of
 //     stage g, so a stage has one barrier and waits for nothing it has just

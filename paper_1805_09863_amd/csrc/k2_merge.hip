@@ -211,10 +211,10 @@ __global__ __launch_bounds__(64 * K2_MAXW) void k2_merge(K2Args a) {
         }
         uint32_t low;
         if (heads == 1) {
-          low = __builtin_amdgcn_readlane((int)lo[0], __builtin_ctzll(won[0]) & 63);
+          low = __builtin_amdgcn_readlane((int)lo[0], __builtin_ctzll(won[0] | 1ull << 63));
 #pragma unroll
           for (int q = 1; q < NQ; ++q) {
-            const uint32_t l = __builtin_amdgcn_readlane((int)lo[q], __builtin_ctzll(won[q]) & 63);
+            const uint32_t l = __builtin_amdgcn_readlane((int)lo[q], __builtin_ctzll(won[q] | 1ull << 63));
             low = won[q] != 0 ? l : low;
           }
         } else {

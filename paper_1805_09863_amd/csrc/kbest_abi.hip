@@ -223,12 +223,12 @@ constexpr TileCost kF32DmaCosts[] = {
 // k rounded up to the k-list lengths the projection kernels are built for
 int kc_of(int k) { return k <= 4 ? 4 : (k <= 8 ? 8 : (k <= 12 ? 12 : 16)); }
 
-// Workgroups of a layout that one CU holds at once.  On the DMA pipeline the
-// 32 x 128 tile (60 KB of LDS, at most 220 registers per lane) and, with
-// k <= 8, the 64 x 128 tile (67 KB, built for at most 256 registers) run two
-// side by side, one's epilogue and barrier waits overlapping the other's
-// products (their grids may reach 512 workgroups); every other tile, and the
-// 64 x 128 one with longer lists, fills a CU.
+// Workgroups of a layout that one CU holds at once.  On the aligned paths (the
+// bf16 DMA pipeline, float32 of 16-byte aligned shapes) the 32 x 128 tile and,
+// with k <= 8, the 64 x 128 tile (both within half of a CU's LDS and 256
+// registers) run two side by side, one's epilogue and barrier waits
+// overlapping the other's products (their grids may reach 512 workgroups);
+// every other tile, and the 64 x 128 one with longer lists, fills a CU.
 int per_cu(int layout, bool dma, int kc) {
   if (!dma) return 1;
   return layout == kb::K1_L32S || (layout == kb::K1_L64 && kc <= 8) ? 2 : 1;
@@ -276,7 +276,7 @@ void pick_by_model(const TileCost (&costs)[n], int N, int H, int V, bool dma, bo
 // KB_TILE=<rows>x<words> (e.g. 32x256) at call time replaces the modelled
 // choice by that tile where the step's path has it (for measuring the cost
 // model; the tuning script sets it): 128x256, 256x128, 32x512, 32x256,
-// 32x128, 64x256, 64x128 on the DMA pipeline (dma), and 256x256 on the bf16 DMA
+// 32x128, 64x256, 64x128 on the aligned paths (dma), and 256x256 on the bf16 DMA
 // pipeline with V >= 256 (wide_ok).  Other values are ignored.
 // A tile wider than V words is one of them on the register-staged kernel (max_words).
 void apply_tile_override(bool dma, bool wide_ok, int max_words, Plan& p) {

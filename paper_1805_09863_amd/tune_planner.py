@@ -12,12 +12,11 @@ projection kernel of kbest_step is timed with HIP events on its own stream
 
 is fitted by least squares on relative error, and the choice the model
 makes on each shape is compared with the fastest tile measured there.  The
-constants of kF32DmaCosts, kF32Costs and kBf16DmaCosts in csrc/kbest_abi.hip
-come from this script's fit, one per path: --dtype f32 (H 256-2048, multiples
-of 64: the DMA pipeline), f32reg (H 264-2056: the register-staged kernel;
-kF32Costs was fitted at H 256-2048 while those shapes took it) and bf16 (the
-DMA pipeline, H 512-2048 x V 8k-90k x 40-2,560 rows); float32 over V 8k-60k x
-40-1,280 rows; k = 5.
+planner's tables in csrc/kbest_abi.hip come from this script's fits, one per
+path (k = 5): --dtype f32 (aligned shapes, H 256-2048, multiples of 64, V
+8k-60k, 40-1,280 rows: kF32DmaCosts), f32reg (H 264-2056: kF32Costs), bf16
+(the DMA pipeline, H 512-2048, V 8k-90k, 40-2,560 rows: kBf16DmaCosts) and
+bf16reg (H 500-2000, odd V of 8,001-90,001, 12-2,560 rows: kBf16Costs).
 
     python -m paper_1805_09863_amd.tune_planner --dtype bf16 --out gpurun_out/tune_bf16.json
 
@@ -61,7 +60,7 @@ GRIDS = {
 
 def per_cu(dtype, tile: str) -> int:
     """Workgroups one CU holds at once, as the planner counts them at k <= 8:
-    two of the DMA pipeline's 32 x 128 and 64 x 128 tiles, one of every other."""
+    two of the aligned paths' 32 x 128 and 64 x 128 tiles, one of every other."""
     return 2 if dtype in ("f32", "bf16") and tile in ("32x128", "64x128") else 1
 
 
@@ -207,10 +206,8 @@ def main():
         log(json.dumps({k: v for k, v in res.items() if k.startswith(("sum", "worst"))}))
         return
     model = fit(rows, grid["tiles"], args.dtype)
-    # the register-staged float32 planner leaves out the 256-row tile (it fits the model poorly)
-    used = {t: m for t, m in model.items() if not (args.dtype == "f32reg" and t == "256x128")}
     res = {"dtype": args.dtype, "grid": {k: list(v) for k, v in grid.items()}, "rows": rows,
-           "fit": model, "evaluation_of_the_planner_set": evaluate(rows, used, args.dtype)}
+           "fit": model, "evaluation_of_the_planner_set": evaluate(rows, model, args.dtype)}
     with open(args.out, "w") as f:
         json.dump(res, f)
     for t, m in model.items():
