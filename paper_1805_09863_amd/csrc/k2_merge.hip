@@ -14,8 +14,9 @@
 //   * the row's best words: rounds of a wave-wide maximum of the scores'
 //     ordered bits, then of the words where heads share a score (wave_keys.hpp),
 //     over the heads of the P sorted split lists (strict total order).  5 rows of
-//     125 splits: k = 10 17.9 -> 16.6 us a step against maxima of both every round.  Each lane keeps its lists' heads and the entries
-//     after them in registers, so a round reads no LDS on its critical path.
+//     125 splits: k = 10 17.9 -> 16.6 us a step against maxima of both every
+//     round.  Each lane keeps its lists' heads and the entries after them in
+//     registers, so a round reads no LDS on its critical path.
 //     The rounds stop once a score (prev + x - LSE) falls below the sentence's
 //     k-th best so far: the row's later entries are worse still;
 //   * the running k best of the sentence and the chunk's candidates are ranked
