@@ -107,7 +107,14 @@ __device__ __forceinline__ uint64_t cand_key(float x, int word) {
 // picked out by its position with a tree of selects, NV - 1 instructions, as
 // often as the wave's busiest lane has candidates.
 
-// Bit 31 - i set: x[i] >= t.
+// The threshold t as pass_mask compares with it, so that the sign of x - t is
+// that of x >= t for every x but NaN: +0 becomes -0 (-0 - +0 is -0, though the
+// two are equal), +inf the largest number (inf - inf is NaN; a threshold may
+// be lower than it need be, and what passes is ranked by its key).
+__device__ __forceinline__ float pass_floor(float t) { return t == 0.f ? -0.f : fminf(t, FLT_MAX); }
+
+// Bit 31 - i set: x[i] >= t, t a pass_floor.  A NaN's bit may be either:
+// whoever picks the candidates leaves it out.
 template <int NV>
 __device__ __forceinline__ uint32_t pass_mask(const float (&x)[NV], float t) {
   uint32_t below = 0;
@@ -351,7 +358,7 @@ struct Epilogue {
 #pragma unroll
       for (int hb = 0; hb < WH; ++hb) {
         const int hl = (wh * WH + hb) * 32 + col;
-        const float t = fmaxf(ep.thr[hl], key2f(tg[hb]));
+        const float t = pass_floor(fmaxf(ep.thr[hl], key2f(tg[hb])));
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
           if (__builtin_amdgcn_ballot_w64(tmax[hb][w] >= t) == 0ull) {
@@ -367,13 +374,13 @@ struct Epilogue {
             const int p = __builtin_clz(m | 1u);
             const uint32_t bit = 0x80000000u >> p;
             const float cx = pick<NV>(x, p);
-            if (m != 0) {
+            if (m != 0 && cx == cx) {
               const int at = __hip_atomic_fetch_add(&ep.cnt[hl], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
               const uint64_t key = cand_key(cx, vbase + pos_word(p));  // while the slot is on its way
               ep.u.pool[hl][min(at, X::PC)] = key;                    // slot PC is nobody's
               kept |= at < X::PC ? 0u : bit;
-              m &= ~bit;
             }
+            m &= ~bit;
           }
           left[hb][w] = kept;
           any |= kept;
