@@ -41,7 +41,8 @@
  *    tile instead where its path has it: 128x256, 256x128, 32x512, 32x256,
  *    32x128 or 64x256 on every path, 64x128 on KB_KERNEL_DMA shapes, and
  *    256x256 on bf16 ones with V >= 256.  Other values are ignored, and on the
- *    register-staged kernel tiles wider than V.  It exists to measure the
+ *    register-staged kernel tiles wider than V; its shapes of H < 32, V < 128
+ *    or V > 2^25 have 128x256, 32x512 and 32x128.  It exists to measure the
  *    model (paper_1805_09863_amd/tune_planner.py); the workspace size follows
  *    it, so size the workspace with the same setting.
  *  - Size limits (KB_ERR_UNSUPPORTED beyond them): N * V <= INT_MAX (a
@@ -118,8 +119,8 @@ size_t kb_kbest_workspace_bytes(int dtype, int N, int H, int V, int k, int S);
 #define KB_KERNEL_DMA 2  /* other tiles on the matrix cores, 16-byte aligned     */
                          /* shapes: bf16 the LDS DMA pipeline, float32 (split    */
                          /* into bf16 pieces) staged through registers           */
-#define KB_KERNEL_REG 3  /* matrix cores, operands staged through registers,  */
-                         /* any shape and alignment                              */
+#define KB_KERNEL_REG 3  /* matrix cores, operands staged through registers or */
+                         /* read by them directly, any shape and alignment       */
 #define KB_PLAN_KERNEL 0
 #define KB_PLAN_TILE_ROWS 1
 #define KB_PLAN_TILE_WORDS 2

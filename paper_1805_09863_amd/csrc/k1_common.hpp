@@ -259,7 +259,7 @@ struct Epilogue {
     const int k = a.k;
 
     // ---- bias (Algorithm 3 AddBias, fused) and masking of words >= V or < vlo
-    const bool ragged = v0 + L::BV > a.V || v0 < vlo;
+    const bool ragged = v0 > a.V - L::BV || v0 < vlo;
 #pragma unroll
     for (int vb = 0; vb < WV; ++vb) {
       const int vl = (wv * WV + vb) * 32 + 4 * half;
@@ -280,7 +280,7 @@ struct Epilogue {
           const int v = v0 + vl + 8 * (r >> 2) + (r & 3);
 #pragma unroll
           for (int hb = 0; hb < WH; ++hb)
-            if (v >= a.V || v < vlo) acc[vb][hb][r] = -INFINITY;
+            if ((uint32_t)v >= (uint32_t)a.V || v < vlo) acc[vb][hb][r] = -INFINITY;
         }
       }
     }

@@ -1,5 +1,5 @@
-// K1, register-staged variant: the fused output-layer projection for every
-// shape and alignment, in bf16 and in float32, all on the bf16 matrix cores.
+// K1, register-staged variant: the fused output-layer projection for shapes of
+// every alignment, in bf16 and in float32, all on the bf16 matrix cores.
 //
 // Operands go global -> registers -> LDS -> fragments, each step one or more
 // stages ahead of the products:
@@ -9,8 +9,7 @@
 //     early enough to end at H, and its states that earlier stages have had
 //     are made zero in h; the last tile of a ragged V starts early enough to
 //     end at V, and the epilogue masks the words that the tile before has had.
-//     (GUARD: the form for H below a stage, V below a tile or beyond 2^25,
-//     which loads element by element);
+//     (H below a stage, V below a tile or beyond 2^25: the direct kernel);
 //   * a stage in LDS is GROUPS groups of 16 states.  bf16: 32 states, two
 //     groups.  float32: 16 states (the smallest tile 32), three groups for
 //     each 16, the pieces of the split below.  W keeps its V-contiguous rows
@@ -35,30 +34,13 @@
 
 #include <type_traits>
 
-#include "k1_common.hpp"
+#include "k1_direct.hpp"
 
 namespace kb {
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t stage16 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-#define KB_GLOBAL __attribute__((address_space(1)))
-
-template <bool F32>
-struct StageTy;
-template <>
-struct StageTy<false> {
-  using E = uint16_t;
-  typedef stage16 V16 __attribute__((aligned(2)));  // 16 bytes at any element
-  static constexpr int EPC = 8, PIECES = 1, PRODS = 1;
-};
-template <>
-struct StageTy<true> {
-  using E = float;
-  typedef stage16 V16 __attribute__((aligned(4)));
-  static constexpr int EPC = 4, PIECES = 3, PRODS = 6;
-};
 
 // (W piece, h piece) of product p
 __device__ constexpr int prod_w(int p) {
@@ -124,13 +106,12 @@ constexpr int stage_waves() {
   return L::BV == 128 && (L::BH == 32 || (L::BH == 64 && KC <= 8)) ? 2 : 1;
 }
 
-template <class L, int KC, bool F32, bool GUARD>
+template <class L, int KC, bool F32>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(stage_waves<L, KC>())))
 void k1_stage(K1Args a) {
   using T = StageTy<F32>;
   using G = StageGeom<L, F32>;
   using E = typename T::E;
-  using GP = const KB_GLOBAL E*;
   constexpr int BV = L::BV, BH = L::BH, WV = L::WV, WH = L::WH, NWV = L::NWV;
   constexpr int BK = G::BK, EPC = T::EPC, PIECES = T::PIECES, GROUPS = G::GROUPS, NSET = G::NSET, HS = G::HS;
   constexpr int ESZ = sizeof(E);
@@ -168,14 +149,14 @@ void k1_stage(K1Args a) {
   for (int i = 0; i < G::W_OPS; ++i) woff[i] = ((uint32_t)wr(i) * (uint32_t)V + (uint32_t)wc(i)) * ESZ;
 #pragma unroll
   for (int i = 0; i < G::H_OPS; ++i) hoff[i] = ((uint32_t)hrow(i) * (uint32_t)H + (uint32_t)kc) * ESZ;
-  auto tile_v0 = [&](int vt) { return GUARD ? vt * BV : min(vt * BV, V - BV); };
+  auto tile_v0 = [&](int vt) { return min(vt * BV, V - BV); };
 
   stage16 R[NSET][G::OPS];
   // the split's tiles are split, split + P, split + 2 P, ... (as in the DMA kernel)
   int ivt = split, ik0 = 0;  // the next stage to load; past the end, the last one again (never used)
   const KB_GLOBAL char *wb, *hb;  // its first W row and h column
   auto set_base = [&]() {
-    const int k = GUARD ? ik0 : min(ik0, H - BK);
+    const int k = min(ik0, H - BK);
     wb = Wg + ((size_t)k * V + tile_v0(ivt)) * ESZ;
     hb = Hg + (size_t)k * ESZ;
   };
@@ -184,20 +165,7 @@ void k1_stage(K1Args a) {
   // compiler wait for younger ones than it needs)
   auto load = [&](stage16 (&r)[G::OPS], int i) __attribute__((always_inline)) {
     const bool w = i < G::W_OPS;
-    if constexpr (GUARD) {
-      E t[EPC];
-#pragma unroll
-      for (int e = 0; e < EPC; ++e) {
-        t[e] = E(0);
-        if (w)  // rows past H meet states that are zero; words past V are masked
-          t[e] = ((GP)Wg)[(size_t)min(ik0 + wr(i), H - 1) * V + min(tile_v0(ivt) + wc(i) + e, V - 1)];
-        else if (ik0 + kc + e < H)
-          t[e] = ((GP)Hg)[(size_t)hrow(i - G::W_OPS) * H + ik0 + kc + e];
-      }
-      r[i] = __builtin_bit_cast(stage16, t);
-    } else {
-      r[i] = *(const KB_GLOBAL typename T::V16*)(w ? wb + woff[i] : hb + hoff[i - G::W_OPS]);
-    }
+    r[i] = *(const KB_GLOBAL typename T::V16*)(w ? wb + woff[i] : hb + hoff[i - G::W_OPS]);
   };
   auto next_stage = [&]() {
     const bool next = ik0 + BK >= nkp * BK;
@@ -208,9 +176,9 @@ void k1_stage(K1Args a) {
   };
 
   // stage k2 >= nk - 1 of a tile: states that earlier stages have had, the
-  // first z of it, become zero (the guarded loads give zeros themselves)
+  // first z of it, become zero
   auto zero_tail = [&](stage16 (&r)[G::OPS], int k2) __attribute__((always_inline)) {
-    if (GUARD || (k2 + 1) * BK <= H) return;
+    if ((k2 + 1) * BK <= H) return;
     const int z = (k2 + 1) * BK - H;
 #pragma unroll
     for (int i = G::W_OPS; i < G::OPS; ++i)
@@ -380,31 +348,18 @@ void k1_stage(K1Args a) {
   epi.finish(ep, a, h0, split);
 }
 
-template <class L, int KC, bool F32>
-hipError_t launch_k1_stage_kc(bool guard, dim3 grid, const K1Args& a, hipStream_t st) {
-  if constexpr (L::BH == 32 && L::BV == 128) {
-    if (guard) {
-      k1_stage<L, KC, F32, true><<<grid, dim3(256), 0, st>>>(a);
-      return hipGetLastError();
-    }
-  } else if (guard) {
-    return hipErrorInvalidValue;
-  }
-  k1_stage<L, KC, F32, false><<<grid, dim3(256), 0, st>>>(a);
-  return hipGetLastError();
-}
-
 template <class L, bool F32>
 hipError_t launch_k1_stage(int kc, dim3 grid, const K1Args& a, hipStream_t st) {
-  const bool guard = stage_guarded(a.H, a.V);
-  if (!guard && a.V < L::BV) return hipErrorInvalidValue;
+  if (direct_shape(a.H, a.V) || a.V < L::BV) return hipErrorInvalidValue;
+  const dim3 block(256);
   switch (kc) {
-    case 4: return launch_k1_stage_kc<L, 4, F32>(guard, grid, a, st);
-    case 8: return launch_k1_stage_kc<L, 8, F32>(guard, grid, a, st);
-    case 12: return launch_k1_stage_kc<L, 12, F32>(guard, grid, a, st);
-    case 16: return launch_k1_stage_kc<L, 16, F32>(guard, grid, a, st);
+    case 4: k1_stage<L, 4, F32><<<grid, block, 0, st>>>(a); break;
+    case 8: k1_stage<L, 8, F32><<<grid, block, 0, st>>>(a); break;
+    case 12: k1_stage<L, 12, F32><<<grid, block, 0, st>>>(a); break;
+    case 16: k1_stage<L, 16, F32><<<grid, block, 0, st>>>(a); break;
     default: return hipErrorInvalidValue;
   }
+  return hipGetLastError();
 }
 
 }  // namespace kb

@@ -98,10 +98,12 @@ __device__ __forceinline__ void k1_cell(const K1Args& a, int b, int& row_tile, i
 enum K1Layout { K1_L256 = 0, K1_L128 = 1, K1_L32 = 2, K1_W256 = 3, K1_L32M = 4, K1_L32S = 5, K1_L64 = 6, K1_L64M = 7 };
 
 // dma: the LDS-DMA pipeline (bf16, H % 128 == 0, V % 8 == 0, 16-byte aligned h and W);
-// layout K1_W256 (256 x 256 tiles) exists only with it.  Everything else is staged
-// through registers (k1_stage.hpp), whose tiles are no wider than the vocabulary.
-// stage_guarded: the shapes that kernel takes element by element, with 32 x 128 tiles.
-inline bool stage_guarded(int H, int V) { return H < 32 || V < 128 || V > (1 << 25); }
+// layout K1_W256 (256 x 256 tiles) exists only with it.  direct_shape: what the direct
+// kernel takes of everything else (k1_direct.hpp; K1_L128, K1_L32 and K1_L32S).  The rest
+// is staged through registers (k1_stage.hpp), whose loads of 16 bytes need a whole stage
+// of states and tiles no wider than the vocabulary, and whose 32-bit offsets reach 32
+// rows of W.
+inline bool direct_shape(int H, int V) { return H < 32 || V < 128 || V > (1 << 25); }
 hipError_t launch_k1(int bf16, int dma, int layout, int kc, dim3 grid, const K1Args& a, hipStream_t st);
 hipError_t launch_zero_u32(uint32_t* p, int n, hipStream_t st);
 

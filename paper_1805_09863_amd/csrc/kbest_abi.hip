@@ -34,11 +34,15 @@ hipError_t launch_k1_dma_L64(int kc, dim3 grid, const K1Args& a, hipStream_t st)
 hipError_t launch_k1_stage_bf16_L64M(int kc, dim3 grid, const K1Args& a, hipStream_t st);
 hipError_t launch_k1_stage_f32_L64M(int kc, dim3 grid, const K1Args& a, hipStream_t st);
 hipError_t launch_k1_dma_L64M(int kc, dim3 grid, const K1Args& a, hipStream_t st);
+hipError_t launch_k1_direct_bf16(int layout, int kc, dim3 grid, const K1Args& a, hipStream_t st);
+hipError_t launch_k1_direct_f32(int layout, int kc, dim3 grid, const K1Args& a, hipStream_t st);
 hipError_t launch_k1_wide(int kc, dim3 grid, const K1Args& a, hipStream_t st);
 
-// float32 is always staged through registers, where it is split; dma: bf16
-// operands the LDS DMA pipeline takes
+// float32 of other than direct shapes is staged through registers, where it is
+// split; dma: bf16 operands the LDS DMA pipeline takes
 hipError_t launch_k1(int bf16, int dma, int layout, int kc, dim3 grid, const K1Args& a, hipStream_t st) {
+  if (direct_shape(a.H, a.V) && !(bf16 && dma))
+    return bf16 ? launch_k1_direct_bf16(layout, kc, grid, a, st) : launch_k1_direct_f32(layout, kc, grid, a, st);
   if (!bf16) {
     switch (layout) {
       case K1_L256: return launch_k1_stage_f32_L256(kc, grid, a, st);
@@ -102,6 +106,7 @@ constexpr int kTargetCUs = 256;
 struct Plan {
   int layout, kc, BH, BV;
   int row_tiles, n_vtiles, P, tps;
+  int per;  // workgroups that a CU holds at once
   size_t stats_off, lists_off, gthr_off, gmax_off, bytes;
 };
 
@@ -220,6 +225,21 @@ constexpr TileCost kF32DmaCosts[] = {
     {kb::K1_L64M, 64, 256, 2.6275e-06, 2.0924e-04, 11.986},
 };
 
+// the direct kernel's shapes: fitted to whole steps (H 4-31, V 1,000-90,000,
+// 9-2560 rows, 270 shapes) for the choices they lead to, which are within 0.8%
+// (float32) and 1.4% (bf16) of the fastest measured tile in the geometric mean;
+// at most 45% (9-12 rows, V = 30,001: 32 x 128 tiles and a merge of 235 splits)
+constexpr TileCost kF32DirectCosts[] = {
+    {kb::K1_L128, 128, 256, 2.36e-06, 2.21e-04, 13.4},
+    {kb::K1_L32, 32, 512, 6.18e-06, 2.88e-04, 11.4},
+    {kb::K1_L32S, 32, 128, 4.17e-06, 7.70e-04, 11.8},
+};
+constexpr TileCost kBf16DirectCosts[] = {
+    {kb::K1_L128, 128, 256, 1.08e-06, 1.91e-04, 12.8},
+    {kb::K1_L32, 32, 512, 1.95e-06, 2.02e-04, 11.4},
+    {kb::K1_L32S, 32, 128, 3.84e-06, 6.86e-04, 11.8},
+};
+
 // k rounded up to the k-list lengths the projection kernels are built for
 int kc_of(int k) { return k <= 4 ? 4 : (k <= 8 ? 8 : (k <= 12 ? 12 : 16)); }
 
@@ -278,8 +298,9 @@ void pick_by_model(const TileCost (&costs)[n], int N, int H, int V, bool dma, bo
 // model; the tuning script sets it): 128x256, 256x128, 32x512, 32x256,
 // 32x128, 64x256, 64x128 on the aligned paths (dma), and 256x256 on the bf16 DMA
 // pipeline with V >= 256 (wide_ok).  Other values are ignored.
-// A tile wider than V words is one of them on the register-staged kernel (max_words).
-void apply_tile_override(bool dma, bool wide_ok, int max_words, Plan& p) {
+// A tile wider than V words is one of them on the register-staged kernel
+// (max_words), and one that the direct kernel has not on its shapes (direct).
+void apply_tile_override(bool dma, bool wide_ok, bool direct, int max_words, Plan& p) {
   const char* e = getenv("KB_TILE");
   int r = 0, w = 0;
   char tail = 0;
@@ -294,6 +315,7 @@ void apply_tile_override(bool dma, bool wide_ok, int max_words, Plan& p) {
   else if (r == 64 && w == 256) layout = kb::K1_L64M;
   else if (r == 64 && w == 128 && dma) layout = kb::K1_L64;
   if (layout < 0 || w > max_words) return;
+  if (direct && layout != kb::K1_L128 && layout != kb::K1_L32 && layout != kb::K1_L32S) return;
   p.layout = layout;
   p.BH = r;
   p.BV = w;
@@ -303,7 +325,7 @@ Plan make_plan(int dtype, int N, int H, int V, int k, bool dma, bool vec) {
   Plan p{};
   const bool dma_path = dma && dma_shape(dtype, H, V);
   const bool staged = dtype == KB_F32 || !dma_path;  // the register-staged kernel, few rows aside
-  const bool guarded = staged && kb::stage_guarded(H, V);
+  const bool direct = staged && kb::direct_shape(H, V);
   const int few_cw = kb::few_chunk_words(dtype == KB_BF16);
   const int few_nt = (V + few_cw - 1) / few_cw, few_p = std::min(few_nt, kTargetCUs);
   if (vec && N <= kb::FEW_ROWS && V >= few_cw && few_is_faster(dtype, N, H, V, k) &&
@@ -315,10 +337,11 @@ Plan make_plan(int dtype, int N, int H, int V, int k, bool dma, bool vec) {
     p.BV = few_cw;
   } else if (dma_path && dtype == KB_BF16) {
     pick_by_model(kBf16DmaCosts, N, H, V, true, false, kc_of(k), p);
-  } else if (guarded) {
-    p.layout = kb::K1_L32S;
-    p.BH = 32;
-    p.BV = 128;
+  } else if (direct) {
+    if (dtype == KB_F32)
+      pick_by_model(kF32DirectCosts, N, H, V, false, false, kc_of(k), p);
+    else
+      pick_by_model(kBf16DirectCosts, N, H, V, false, false, kc_of(k), p);
   } else if (dtype == KB_F32) {
     if (dma_path)
       pick_by_model(kF32DmaCosts, N, H, V, true, true, kc_of(k), p);
@@ -327,12 +350,14 @@ Plan make_plan(int dtype, int N, int H, int V, int k, bool dma, bool vec) {
   } else {
     pick_by_model(kBf16Costs, N, H, V, false, true, kc_of(k), p);
   }
-  if (p.layout != kb::K1_FEW && !guarded)
-    apply_tile_override(dma_path, dtype == KB_BF16 && dma_path && V >= kWideMinCols, staged ? V : INT_MAX, p);
+  if (p.layout != kb::K1_FEW)
+    apply_tile_override(dma_path, dtype == KB_BF16 && dma_path && V >= kWideMinCols, direct,
+                        staged && !direct ? V : INT_MAX, p);
   p.kc = kc_of(k);
   p.row_tiles = (N + p.BH - 1) / p.BH;
   p.n_vtiles = (V + p.BV - 1) / p.BV;
-  const int P = splits_for(p.row_tiles, p.n_vtiles, per_cu(p.layout, dma_path, p.kc));
+  p.per = per_cu(p.layout, dma_path && !direct, p.kc);
+  const int P = splits_for(p.row_tiles, p.n_vtiles, p.per);
   p.tps = (p.n_vtiles + P - 1) / P;
   p.P = (p.n_vtiles + p.tps - 1) / p.tps;  // no empty split
   p.stats_off = 0;
@@ -446,7 +471,7 @@ kb_status launch_projection(int dtype, int N, int H, int V, int k, const void* h
   // With one tile per split and every workgroup resident from the start, no
   // workgroup reads a threshold before the others publish theirs: the other
   // tiles' kernels then share none, and the reset is not needed.
-  const bool all_resident = p.P * p.row_tiles <= per_cu(p.layout, dma, p.kc) * kTargetCUs;
+  const bool all_resident = p.P * p.row_tiles <= p.per * kTargetCUs;
   a1.share = (p.layout == kb::K1_W256 || p.tps > 1 || !all_resident) ? 1 : 0;
   hipError_t e = hipSuccess;
   if (p.layout != kb::K1_FEW && a1.share) {  // the few-row kernel shares no thresholds
