@@ -40,9 +40,9 @@ struct StageTy<true> {
 // this wave's blocks of it.  16 states at a time; a lane holds 8 of them, of
 // one word and of one row per block: bf16 8 half + j, float32 8 (j / 4) + 4
 // half + j % 4 (so that a row's 16 bytes are consecutive states; step j of the
-// products pairs the same states of both operands).  The next 32 states are on
+// products pairs the same states of both operands).  AHEAD: the next 32 states are on
 // their way during the products of these.
-template <class L, bool F32>
+template <class L, bool F32, bool AHEAD>
 __device__ __forceinline__ void direct_products(f32x16 (&acc)[L::WV][L::WH], const K1Args& a, int h0, int v0) {
   using T = StageTy<F32>;
   using E = typename T::E;
@@ -133,6 +133,18 @@ __device__ __forceinline__ void direct_products(f32x16 (&acc)[L::WV][L::WH], con
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[vb][hb][r] = 0.f;
   const int whole = H / 16;
+  if constexpr (!AHEAD) {
+    Chunk c;
+    if (H % 16 != 0) {
+      load_tail(16 * whole, c);
+      products(c);
+    }
+    for (int i = 0; i < whole; ++i) {
+      load(16 * i, c);
+      products(c);
+    }
+    return;
+  }
   Chunk c0, c1, c2;
   auto chunk = [&](int c) { return 16 * min(c, whole - 1); };  // past the last: that one again, unused
   if (H % 16 != 0) load_tail(16 * whole, c0);
@@ -155,15 +167,11 @@ __device__ __forceinline__ void direct_products(f32x16 (&acc)[L::WV][L::WH], con
   }
 }
 
-template <class L, int KC, bool F32>
-__global__ __launch_bounds__(256) void k1_direct(K1Args a) {
-  constexpr int BV = L::BV, BH = L::BH;
-  __shared__ __attribute__((aligned(16))) SmemEpi<L, KC> ep;
+// A whole cell: every tile of the split against the rows from h0.
+template <class L, int KC, bool F32, bool AHEAD>
+__device__ __forceinline__ void direct_cell(SmemEpi<L, KC>& ep, const K1Args& a, int h0, int split) {
+  constexpr int BV = L::BV;
   const int tid = threadIdx.x;
-  int row_tile, split;
-  k1_cell(a, blockIdx.x, row_tile, split);
-  const int h0 = row_tile * BH;
-
   Epilogue<L, KC> epi;
   epi.init(ep, a.k);
   // the split's tiles are split, split + P, split + 2 P, ... (as in the other kernels)
@@ -172,13 +180,21 @@ __global__ __launch_bounds__(256) void k1_direct(K1Args a) {
     uint32_t tg[L::WH];
     epi.load_shared_thr(a, h0, tg);
     f32x16 acc[L::WV][L::WH];
-    direct_products<L, F32>(acc, a, h0, v0);
+    direct_products<L, F32, AHEAD>(acc, a, h0, v0);
     // (the tile before has been through with its bias since its first barrier)
     for (int i = tid; i < BV; i += 256) ep.bias[0][i] = a.b[min((uint32_t)v0 + i, (uint32_t)a.V - 1)];
     lds_barrier();
     epi.tile(acc, ep, a, h0, v0, v0, vt == split, tg, ep.bias[0]);
   }
   epi.finish(ep, a, h0, split);
+}
+
+template <class L, int KC, bool F32>
+__global__ __launch_bounds__(256) void k1_direct(K1Args a) {
+  __shared__ __attribute__((aligned(16))) SmemEpi<L, KC> ep;
+  int row_tile, split;
+  k1_cell(a, blockIdx.x, row_tile, split);
+  direct_cell<L, KC, F32, true>(ep, a, row_tile * L::BH, split);
 }
 
 template <class L, bool F32>

@@ -345,7 +345,27 @@ void k1_stage(K1Args a) {
     for (int u = 0; u < READS; ++u) read(S[0], u, F[0]);
     lds_barrier();  // every wave has read buffer 0
   }
-  epi.finish(ep, a, h0, split);
+
+  // An infinite operand leaves NaN among these products where its own is an
+  // infinity: its pieces are inf and inf - inf, and states and pieces of zero
+  // meet it.  A NaN stays in its row's sum, so a cell that ends with one is
+  // done again as the direct kernel does it (whose infinities are the
+  // operands' own).  Without the shared thresholds: those that this pass has
+  // published are its own words', whose scores may come out an ulp lower.
+  bool nan = false;
+#pragma unroll
+  for (int hb = 0; hb < WH; ++hb) nan |= epi.st_s[hb] != epi.st_s[hb];
+  if (nan) ep.flag[0] = 1;
+  lds_barrier();
+  const bool again = ep.flag[0] != 0;
+  lds_barrier();
+  if (!again) {
+    epi.finish(ep, a, h0, split);
+  } else {
+    K1Args d = a;
+    d.share = 0;
+    direct_cell<L, KC, F32, false>(ep, d, h0, split);
+  }
 }
 
 template <class L, bool F32>
