@@ -93,10 +93,13 @@ __device__ __forceinline__ float key2f(uint32_t k) {
 
 // 64-bit order key of a (score, word) candidate: higher score first, then
 // lower word (the strict-'>' scans of the paper).  -0 is folded into +0 so
-// that equal scores compare equal.  0 is no candidate's key.
+// that equal scores compare equal, and a NaN into -inf, which no score that
+// passes the filter has (leaving NaNs out where they are picked, by a test of
+// every candidate, took 1% of a step).  0 is no candidate's key.
 __device__ __forceinline__ uint64_t cand_key(float x, int word) {
-  return ((uint64_t)f2key(x + 0.0f) << 32) | (uint32_t)~(uint32_t)word;
+  return ((uint64_t)f2key(fmaxf(x, -INFINITY) + 0.0f) << 32) | (uint32_t)~(uint32_t)word;
 }
+constexpr uint32_t kNegInfKey = 0x007FFFFFu;  // f2key(-inf)
 
 // ------------------------------------------------------------ candidates of a lane
 // A lane holds NV (16 or 32) scores of a row in registers, and few of them
@@ -113,8 +116,8 @@ __device__ __forceinline__ uint64_t cand_key(float x, int word) {
 // be lower than it need be, and what passes is ranked by its key).
 __device__ __forceinline__ float pass_floor(float t) { return t == 0.f ? -0.f : fminf(t, FLT_MAX); }
 
-// Bit 31 - i set: x[i] >= t, t a pass_floor.  A NaN's bit may be either:
-// whoever picks the candidates leaves it out.
+// Bit 31 - i set: x[i] >= t, t a pass_floor.  A NaN's bit may be either (its
+// key is that of -inf).
 template <int NV>
 __device__ __forceinline__ uint32_t pass_mask(const float (&x)[NV], float t) {
   uint32_t below = 0;
@@ -374,13 +377,13 @@ struct Epilogue {
             const int p = __builtin_clz(m | 1u);
             const uint32_t bit = 0x80000000u >> p;
             const float cx = pick<NV>(x, p);
-            if (m != 0 && cx == cx) {
+            if (m != 0) {
               const int at = __hip_atomic_fetch_add(&ep.cnt[hl], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
               const uint64_t key = cand_key(cx, vbase + pos_word(p));  // while the slot is on its way
               ep.u.pool[hl][min(at, X::PC)] = key;                    // slot PC is nobody's
               kept |= at < X::PC ? 0u : bit;
+              m &= ~bit;
             }
-            m &= ~bit;
           }
           left[hb][w] = kept;
           any |= kept;
@@ -515,8 +518,9 @@ struct Epilogue {
     const int n = min(L::BH, a.N - h0) * k;
     for (int i = tid; i < n; i += 256) {
       const uint64_t key = ep.lst[i / k][i % k];
-      out[i] = key != 0ull ? make_int2(__float_as_int(key2f((uint32_t)(key >> 32))), (int)~(uint32_t)key)
-                           : make_int2(__float_as_int(-INFINITY), INT_MAX);
+      const uint32_t score = (uint32_t)(key >> 32);  // (0: no candidate)
+      out[i] = score > kNegInfKey ? make_int2(__float_as_int(key2f(score)), (int)~(uint32_t)key)
+                                  : make_int2(__float_as_int(-INFINITY), INT_MAX);
     }
   }
 };

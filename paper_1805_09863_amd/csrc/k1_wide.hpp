@@ -507,13 +507,13 @@ __global__ __launch_bounds__(256, 1) void k1_wide(K1Args a) {
             const int p = __builtin_clz(m | 1u);
             const uint32_t bit = 0x80000000u >> p;
             const float cx = pick<32>(x, p);
-            if (m != 0 && cx == cx) {
+            if (m != 0) {
               const int at = __hip_atomic_fetch_add(&ep.cnt[rl], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
               const uint64_t key = cand_key(cx, vbase + pos_word(p));  // while the slot is on its way
               *(KB_LDS uint64_t*)(uintptr_t)pool_at(pool, over, rl, min(at, G::PC)) = key;
               kept |= at < G::PC ? 0u : bit;
+              m &= ~bit;
             }
-            m &= ~bit;
           }
           left[hb][w] = kept;
           any |= kept;
