@@ -72,7 +72,10 @@ typedef enum kb_status {
 
 /* Storage type of h and W.  Bias, scores and all accumulation are float32. */
 typedef enum kb_dtype {
-  KB_F32 = 0,  /* float32 h and W; float32 products on the matrix cores      */
+  KB_F32 = 0,  /* float32 h and W; float32 products on the matrix cores, from */
+               /* H = 32 up as products of three bf16 pieces: to float32     */
+               /* rounding for operands of at least 2^-109 in magnitude,     */
+               /* smaller ones to an absolute 2^-133                         */
   KB_BF16 = 1  /* bfloat16 h and W (the half-precision GEMM of Section 2.3);  */
                /* exact bf16 x bf16 products, float32 accumulation           */
 } kb_dtype;

@@ -21,15 +21,20 @@
 //     stage g, so a stage has one barrier and waits for nothing it has just
 //     asked for.
 //
-// float32: each operand is split into three bf16 pieces whose sum is the
-// operand exactly (8 + 8 + 8 significant bits: the first truncated, so that it
-// cannot overflow, the second rounded to nearest, the third what is left), and
-// a product is the six piece products of weight 2^-16 and above, each exact,
-// accumulated in float32.  The three left out are below 2^-22 of the product,
-// with signs that do not lean either way; measured against 64 bits the scores'
-// error is no larger than with the float32 matrix instruction, whose sums take
-// a rounding every two states.  Six bf16 products of 32 cycles replace eight
-// float32 ones of 64.
+// float32: each operand is split into three bf16 pieces (8 + 8 + 8 significant
+// bits, the first two rounded to nearest, the third what is left), whose sum
+// is the operand exactly from 2^-109 up; below, where the third piece nears
+// bf16's smallest subnormal of 2^-133, it is off by up to that.  A product
+// is the six piece products of weight 2^-16 and above, each exact, accumulated
+// in float32.  The three left out are below 2^-24 of the product together,
+// with signs that do not lean either way.  Against 64 bits, relative to the
+// root of the sum of squares of the products, the error is 2.6e-8 up to 16
+// states (at most 1.5e-7), where the float32 matrix instruction, which rounds
+// its sum every two states, has 2.5e-8 for one or two (at most 6e-8 and 8e-8),
+// 3.1e-8 for four, 5.4e-8 (4.0e-7) for 16: no less precise from three states
+// on.  (A first piece cut off, not rounded, left out up to 2^-22: 3.4e-8, at
+// most 2.4e-7.)  An operand that rounds to infinity, within 2^-9 of FLT_MAX,
+// counts as infinite below.  Six bf16 products of 32 cycles replace eight float32 ones of 64.
 #pragma once
 
 #include <type_traits>
@@ -55,9 +60,9 @@ __device__ constexpr int prod_h(int p) {
 // The three bf16 pieces of two floats, each pair packed, in two parts of five
 // and six instructions: the first piece and what it leaves, then the other two.
 __device__ __forceinline__ void split_first(uint32_t u0, uint32_t u1, uint32_t& p0, f32x2& rest) {
-  p0 = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
-  rest = f32x2{__uint_as_float(u0) - __uint_as_float(u0 & 0xFFFF0000u),
-               __uint_as_float(u1) - __uint_as_float(u1 & 0xFFFF0000u)};
+  const f32x2 x{__uint_as_float(u0), __uint_as_float(u1)};
+  p0 = __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
+  rest = f32x2{x[0] - __uint_as_float(p0 << 16), x[1] - __uint_as_float(p0 & 0xFFFF0000u)};
 }
 __device__ __forceinline__ void split_rest(f32x2 r, uint32_t& p1, uint32_t& p2) {
   p1 = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2));
@@ -346,9 +351,9 @@ void k1_stage(K1Args a) {
     lds_barrier();  // every wave has read buffer 0
   }
 
-  // An infinite operand leaves NaN among these products where its own is an
-  // infinity: its pieces are inf and inf - inf, and states and pieces of zero
-  // meet it.  A NaN stays in its row's sum, so a cell that ends with one is
+  // An infinite operand (in float32 also one whose first piece is) leaves NaN
+  // among these products where its own is an infinity or a number: its pieces
+  // are inf and inf - inf, and states and pieces of zero meet it.  A NaN stays in its row's sum, so a cell that ends with one is
   // done again as the direct kernel does it (whose infinities are the
   // operands' own).  Without the shared thresholds: those that this pass has
   // published are its own words', whose scores may come out an ulp lower.

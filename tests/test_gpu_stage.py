@@ -65,32 +65,44 @@ def test_operands_at_odd_addresses(kb, dt, tile, monkeypatch):
         check(inp, tuple(x.cpu().numpy() for x in out))
 
 
-def test_float32_split_carries_every_bit(kb):
+@pytest.mark.parametrize("values", ["ordinary", "cut", "small", "largest"])
+def test_float32_split_carries_every_bit(kb, values):
     # greedy scores of one-hot states are single products h * w, plus zeros:
     # the pieces' products must give them to float32 rounding, whatever the
-    # magnitudes: next to FLT_MAX (whose bf16 rounding would be infinite),
-    # all significant bits set, and small normal numbers
+    # magnitudes and bits.  Each row of W has its largest entry, the one that is
+    # read back, at a random word.
     g = np.random.default_rng(5)
-    H, V, N = 64, 1024, 64
-    big = np.float32(3.4028235e38)
-    W = (g.standard_normal((H, V)) * np.exp2(g.integers(-20, 20, (H, 1)))).astype(np.float32)
-    scale = np.exp2(g.integers(-30, 30, N)).astype(np.float32)
+    H, V, N = 64, 1024, 2048
+    W = (0.4 * g.random((H, V))).astype(np.float32)
+    top = 1.0 + g.random(H)             # 24 random bits
+    state = 1.0 + g.random(N)
+    if values == "cut":                 # first pieces cut off, not rounded, would leave most behind
+        top[:] = 1 + 2.0 ** -7 - 2.0 ** -16
+        state[::2] = 1 + 2.0 ** -7 - 2.0 ** -16
+    W[np.arange(H), g.integers(0, V, H)] = top
+    state = state.astype(np.float32) * np.exp2(g.integers(-20, 20, N)).astype(np.float32)
+    W *= np.exp2(g.integers(-20, 20, (H, 1))).astype(np.float32)
+    if values == "small":               # weights whose third pieces are subnormal in bf16, the smallest exact ones
+        W *= np.float32(2.0 ** -109) / np.exp2(np.floor(np.log2(W.max(1, keepdims=True))))
+        state = np.abs(state) * np.float32(2.0 ** 60)
+    if values == "largest":             # next to FLT_MAX, whose rounding to bf16 is infinite
+        W = (W / W.max(1, keepdims=True) * np.float32(3.4028235e38)).astype(np.float32)
+        state = (np.abs(state) * np.float32(2.0 ** -100)).astype(np.float32)
     h = np.zeros((N, H), np.float32)
-    h[np.arange(N), np.arange(H)] = scale * np.float32(1.9999999)
-    W[3] = np.linspace(0.5, 1, V, dtype=np.float32) * big   # W near FLT_MAX against a small state
-    h[3, 3] = np.float32(2.0 ** -120)
-    W[5] = np.float32(2.0 ** -120) * np.linspace(1, 2, V, dtype=np.float32)
-    h[5, 5] = big                                           # a state of FLT_MAX against small weights
+    h[np.arange(N), np.arange(N) % H] = state
     b = np.zeros(V, np.float32)
+    assert kb.kbest_plan(kb.KB_F32, N, H, V, 1)["kernel"] == "dma"
     tok, val = kb.argmax_step(*(torch.from_numpy(x).cuda() for x in (h, W, b)))
     torch.cuda.synchronize()
-    x = h.astype(np.float64) @ W.astype(np.float64)
-    want = x.max(1)
+    col = W.astype(np.float64)[np.arange(N) % H]
+    want = state.astype(np.float64) * col.max(1)
+    assert np.array_equal(tok.cpu().numpy(), col.argmax(1))
     err = np.abs(val.cpu().numpy() - want) / np.abs(want)
-    say(f"largest relative error {err.max():.2e}")
-    # six pieces' products: the three left out are below 2^-22 of the product together, then one float32 rounding each
-    assert err.max() < 2.0 ** -21
-    assert np.allclose(x[np.arange(N), tok.cpu().numpy()], want, rtol=2.0 ** -20)
+    say(f"{values}: largest relative error {err.max():.2e}")
+    # the three products left out are below 2^-24 of the product together; then
+    # the float32 rounding of the sum, and those of the five smaller products'
+    # sums, together below an eighth of it
+    assert err.max() < 2.0 ** -24 * (1 + 1 + 0.125)
 
 
 @pytest.mark.parametrize("dt", ["bf16", "f32"])
