@@ -72,7 +72,7 @@ struct alignas(16) SmemEpi {
   uint32_t tgk[2][L::BH];   // shared-threshold keys read at the tile's first stage
   float thr[L::BH];         // row's local threshold: k-th best score so far, or the seed
   int cnt[L::BH];           // candidates of the row this round (may exceed PC: the rest waits)
-  int flag[2];              // "some lane has candidates left" of the current and the next round
+  int flag[4];              // "some lane has candidates left" of the current and the next round (two used)
   uint64_t lst[L::BH][KC + 1];  // the row's best keys of the split so far, best first; 0: none
   union {
     uint64_t pool[L::BH][X::PC + 1];  // this round's candidates
@@ -208,6 +208,8 @@ struct Epilogue {
   static constexpr int WV = L::WV, WH = L::WH, NWV = L::NWV;
   using X = Sel<L, KC>;
   using Smem = SmemEpi<L, KC>;
+  // the seeds are written and read 16 bytes at a time
+  static_assert(offsetof(Smem, u) % 16 == 0 && X::RS % 4 == 0, "aligned seeds");
   static constexpr int NV = WV >= 2 ? 32 : 16;   // scores per mask
   static constexpr int NW = WV * 16 / NV;        // masks per row and lane
   float st_m[WH], st_s[WH];
