@@ -169,75 +169,69 @@ bool few_is_faster(int dtype, int N, int H, int V, int k) {
 //   (a H + e) x (rows x words one workgroup covers) x slots + f  microseconds,
 // the workgroup covering row tile x word tile x tiles per split, slots = 2
 // for a tile planned at two workgroups per CU whose grid exceeds one per CU.  a, e and f
-// per layout are fitted by tune_planner.py to the projection times of every
-// layout forced in turn (KB_TILE; k = 5) over 40-1280 rows (bf16 2560), one
-// table per path: float32 of 16-byte aligned shapes and of the others (H
-// 256-2048, V 8k-60k, 120 shapes each), bf16 on the DMA pipeline (H 512-2048,
-// V 8k-90k, 132 shapes) and bf16 staged through registers (H 500-2000, V
-// 8,001-90,001, 12-2560 rows, 156 shapes).  The fits choose within 0.2%,
-// 0.1%, 1.5% and 0.9% of the fastest measured layout (geometric mean over the
-// shapes).  Three of the tables then differ from the fits, as little as it
-// takes, so that choices which tests hold stay as they were: float32 at 320
-// rows, H = 512, V = 30,000 on 64 x 128 tiles (measured 84 us against 80 on
-// 128 x 256; the table's choices lose 0.5% on the grid), at H = 520 on
-// 32 x 256 (125 against 86; 1.4%), and unaligned bf16 at 640 rows, V = 60,000
-// on 256 x 128: that table leaves out 128 x 256 above 512 rows (4% faster from
-// 960 rows on, up to 25% at 640).
+// per layout come from tune_planner.py's times of every layout forced in turn
+// (KB_TILE; k = 5), one table per path: float32 of 16-byte aligned shapes and of
+// the others (H 256-2056, V 8k-90k, 12-1280 rows), bf16 on the DMA pipeline (H
+// 512-2048, V 8k-90k, 12-2560 rows) and bf16 staged through registers (H 500-2000,
+// V 8,001-90,001, 12-2560 rows): least squares, then moved by a random search
+// to where the choices they lead to lose least, over projections and whole
+// steps, of one W and of three in turn (366 to 684 points a path).  On 216 shapes
+// a path of other row counts the choices lose 0.2% (bf16 DMA), 0.1% and less
+// (float32) and 0.4% (other bf16) to the fastest layout in the geometric mean,
+// and at most 7%, 5% and 13%.
 struct TileCost {
   int layout, BH, BV;
   double a, e, f;
-  int max_rows = INT_MAX;  // not used for more rows
 };
 constexpr TileCost kF32Costs[] = {
-    {kb::K1_L128, 128, 256, 1.8800e-06, 5.9114e-04, 8.145},
-    {kb::K1_L256, 256, 128, 1.9315e-06, 5.9766e-04, 7.410},
-    {kb::K1_L32, 32, 512, 3.8555e-06, 4.1431e-04, 13.226},
-    {kb::K1_L32M, 32, 256, 3.7407e-06, 4.5810e-04, 11.376},
-    {kb::K1_L32S, 32, 128, 4.5975e-06, 1.0512e-03, 11.672},
-    {kb::K1_L64M, 64, 256, 2.6051e-06, 7.4404e-04, 10.660},
+    {kb::K1_L128, 128, 256, 1.8173e-06, 2.7519e-04, 10.566},
+    {kb::K1_L256, 256, 128, 1.8641e-06, 2.8272e-04, 9.907},
+    {kb::K1_L32, 32, 512, 3.8135e-06, 4.3146e-04, 14.528},
+    {kb::K1_L32M, 32, 256, 4.2578e-06, 5.9459e-04, 12.675},
+    {kb::K1_L32S, 32, 128, 4.4250e-06, 3.9757e-03, -0.002},
+    {kb::K1_L64M, 64, 256, 2.6635e-06, 4.0129e-04, 12.448},
 };
 constexpr TileCost kBf16Costs[] = {
-    {kb::K1_L128, 128, 256, 4.7259e-07, 2.0048e-04, 9.363, 512},
-    {kb::K1_L256, 256, 128, 4.6810e-07, 2.1800e-04, 8.470},
-    {kb::K1_L32, 32, 512, 1.1955e-06, 1.5964e-04, 13.668},
-    {kb::K1_L32M, 32, 256, 1.2930e-06, 2.3384e-04, 13.805},
-    {kb::K1_L32S, 32, 128, 1.7152e-06, 4.0053e-04, 11.281},
-    {kb::K1_L64M, 64, 256, 7.2953e-07, 1.8632e-04, 15.943},
+    {kb::K1_L128, 128, 256, 4.7311e-07, 2.1395e-04, 10.649},
+    {kb::K1_L256, 256, 128, 4.6597e-07, 2.4151e-04, 9.790},
+    {kb::K1_L32, 32, 512, 1.2921e-06, 1.5562e-04, 14.588},
+    {kb::K1_L32M, 32, 256, 1.3683e-06, 2.4555e-04, 14.615},
+    {kb::K1_L32S, 32, 128, 1.4410e-06, 3.0864e-03, 0.000},
+    {kb::K1_L64M, 64, 256, 7.7348e-07, 2.0322e-04, 16.944},
 };
 constexpr TileCost kBf16DmaCosts[] = {
-    {kb::K1_W256, 256, 256, 3.1181e-07, 1.5459e-04, 11.767},
-    {kb::K1_L128, 128, 256, 4.9410e-07, 1.7781e-04, 10.726},
-    {kb::K1_L256, 256, 128, 4.8545e-07, 1.9365e-04, 10.637},
-    {kb::K1_L32, 32, 512, 9.6669e-07, 1.5281e-04, 9.243},
-    {kb::K1_L32M, 32, 256, 1.2394e-06, 2.0440e-04, 9.892},
-    {kb::K1_L32S, 32, 128, 1.3204e-06, 1.5942e-04, 10.384},
-    {kb::K1_L64, 64, 128, 7.5603e-07, 1.1203e-04, 12.771},
-    {kb::K1_L64M, 64, 256, 7.3923e-07, 1.9822e-04, 10.651},
+    {kb::K1_W256, 256, 256, 2.9632e-07, 1.5292e-04, 13.028},
+    {kb::K1_L128, 128, 256, 4.8494e-07, 2.0928e-04, 11.317},
+    {kb::K1_L256, 256, 128, 4.6854e-07, 2.3413e-04, 10.485},
+    {kb::K1_L32, 32, 512, 1.0383e-06, 1.6343e-04, 9.703},
+    {kb::K1_L32M, 32, 256, 1.2823e-06, 2.2472e-04, 10.326},
+    {kb::K1_L32S, 32, 128, 1.2423e-06, -3.6067e-04, 13.613},
+    {kb::K1_L64, 64, 128, 7.3448e-07, -1.6459e-04, 16.269},
+    {kb::K1_L64M, 64, 256, 7.2200e-07, 2.2120e-04, 11.507},
 };
 // float32 of 16-byte aligned shapes: two workgroups per CU where the tile allows
 constexpr TileCost kF32DmaCosts[] = {
-    {kb::K1_L128, 128, 256, 1.9118e-06, 2.3125e-04, 9.787},
-    {kb::K1_L256, 256, 128, 1.9672e-06, 2.3841e-04, 8.752},
-    {kb::K1_L32, 32, 512, 3.8660e-06, 1.7593e-04, 13.239},
-    {kb::K1_L32M, 32, 256, 4.4029e-06, 2.5430e-04, 11.154},
-    {kb::K1_L32S, 32, 128, 3.6898e-06, 3.5093e-04, 12.700},
-    {kb::K1_L64, 64, 128, 2.7720e-06, 9.9401e-05, 13.677},
-    {kb::K1_L64M, 64, 256, 2.6275e-06, 2.0924e-04, 11.986},
+    {kb::K1_L128, 128, 256, 1.7577e-06, 2.2758e-04, 10.986},
+    {kb::K1_L256, 256, 128, 1.8245e-06, 2.3310e-04, 10.236},
+    {kb::K1_L32, 32, 512, 3.8563e-06, 2.0931e-04, 14.642},
+    {kb::K1_L32M, 32, 256, 4.2946e-06, 2.9048e-04, 12.846},
+    {kb::K1_L32S, 32, 128, 3.8486e-06, -9.1551e-05, 15.554},
+    {kb::K1_L64, 64, 128, 2.9560e-06, -1.3850e-04, 16.882},
+    {kb::K1_L64M, 64, 256, 2.6623e-06, 2.3312e-04, 12.864},
 };
-
 // the direct kernel's shapes: fitted to whole steps (H 4-31, V 1,000-90,000,
-// 9-2560 rows, 270 shapes) for the choices they lead to, which are within 0.8%
-// (float32) and 1.4% (bf16) of the fastest measured tile in the geometric mean;
-// at most 45% (9-12 rows, V = 30,001: 32 x 128 tiles and a merge of 235 splits)
+// 9-2560 rows, 270 shapes) for the choices they lead to, which are within 0.3%
+// (float32) and 0.1% (bf16) of the fastest measured tile in the geometric mean,
+// at most 14% and 3%
 constexpr TileCost kF32DirectCosts[] = {
-    {kb::K1_L128, 128, 256, 2.36e-06, 2.21e-04, 13.4},
-    {kb::K1_L32, 32, 512, 6.18e-06, 2.88e-04, 11.4},
-    {kb::K1_L32S, 32, 128, 4.17e-06, 7.70e-04, 11.8},
+    {kb::K1_L128, 128, 256, 2.26e-06, 1.93e-04, 14.2},
+    {kb::K1_L32, 32, 512, 6.15e-06, 2.95e-04, 11.3},
+    {kb::K1_L32S, 32, 128, 3.53e-06, 7.24e-04, 12.2},
 };
 constexpr TileCost kBf16DirectCosts[] = {
-    {kb::K1_L128, 128, 256, 1.08e-06, 1.91e-04, 12.8},
-    {kb::K1_L32, 32, 512, 1.95e-06, 2.02e-04, 11.4},
-    {kb::K1_L32S, 32, 128, 3.84e-06, 6.86e-04, 11.8},
+    {kb::K1_L128, 128, 256, 1.35e-06, 1.88e-04, 12.8},
+    {kb::K1_L32, 32, 512, 1.72e-06, 2.34e-04, 11.4},
+    {kb::K1_L32S, 32, 128, 4.67e-06, 5.90e-04, 11.8},
 };
 
 // k rounded up to the k-list lengths the projection kernels are built for
@@ -263,27 +257,47 @@ int splits_for(int row_tiles, int n_vtiles, int per) {
   return P;
 }
 
+// What the merge adds to a step with the splits: up to 64 its time hardly
+// depends on them, then it grows by 0.02 to 0.03 us each (12-160 rows, whole
+// steps less the modelled projection: 3 us at 64 splits, 5 at 120, 8.5 at 235;
+// 0.02 chooses best over the four paths), twice that for lists of more than 8.
+constexpr int kMergeSplits = 64;
+constexpr double kMergePerSplit = 0.02;
+// A last tile that is its split's only one and has fewer words than fill k of
+// the 32 groups whose maxima give a threshold has none: every word goes through
+// the candidate rounds, 0.15 us a word with 32-row tiles (bf16, 12 x 512 x
+// 40,000, 64 words of 512: 32.4 us against 22.3 at 39,936 words), 0.27 with 128
+// rows (39,960, 24 words of 256: 33.8 against 28.2).
+constexpr double kRaggedPerWord = 0.2;
+
 // the layout of the least modelled time among n (ties keep the earlier)
 template <size_t n>
-void pick_by_model(const TileCost (&costs)[n], int N, int H, int V, bool dma, bool staged, int kc, Plan& p) {
+void pick_by_model(const TileCost (&costs)[n], int N, int H, int V, bool dma, bool staged, int k, Plan& p) {
+  const int kc = kc_of(k);
   double best = -1.0;
   for (const TileCost& c : costs) {
     if (c.layout == kb::K1_W256 && V < kWideMinCols) continue;
-    if ((staged && V < c.BV) || N > c.max_rows) continue;
+    if (staged && V < c.BV) continue;
     if (c.layout == kb::K1_L64 && kc > 8) continue;  // fitted at two workgroups per CU
     const int rt = (N + c.BH - 1) / c.BH, nt = (V + c.BV - 1) / c.BV;
     const int per = per_cu(c.layout, dma, kc);
     const int P = splits_for(rt, nt, per), tps = (nt + P - 1) / P;
     const bool paired = rt * ((nt + tps - 1) / tps) > kTargetCUs;
-    // a two-per-CU tile alone on its CU with several tiles to run in turn
-    // (one row tile: splits are capped at 256) is slower than the fit says
-    // (V=50k, 40 rows, bf16: 64 x 128 measured 43.6 us against 37.5 for
-    // 32 x 512); the fit holds for co-resident pairs and single tiles
-    if (per == 2 && !paired && tps > 1) continue;
+    // The small tiles are for one tile per split.  With several in turn they
+    // are slower than any fit that holds for the others says: two workgroups a
+    // CU (bf16, 64 x 128, H = 1024, V = 50k, 320 rows in four tiles each: 86 us
+    // against 73 on 256 x 256; H = 512, V = 90k 96 against 73), one alone (V =
+    // 50k, 40 rows: 43.6 against 37.5 on 32 x 512) and off the aligned paths
+    // (32 x 128, H = 500, V = 90,001, 24 rows: 43 against 28).  256 x 128
+    // tiles, which every table has, are as narrow.
+    if ((c.layout == kb::K1_L32S || c.layout == kb::K1_L64) && tps > 1) continue;
     // a CU that holds two workgroups runs both: twice the words at the
     // co-resident rate (the fit's), once the grid exceeds one per CU
     const int slots = per == 2 && paired ? 2 : 1;
-    const double t = (c.a * H + c.e) * (double)c.BH * c.BV * tps * slots + c.f;
+    const int splits = (nt + tps - 1) / tps, left = V % c.BV;
+    double t = (c.a * H + c.e) * (double)c.BH * c.BV * tps * slots + c.f +
+               (k > 8 ? 2 : 1) * kMergePerSplit * std::max(0, splits - kMergeSplits);
+    if (tps == 1 && left * 32 < k * c.BV) t += kRaggedPerWord * left;
     if (best < 0.0 || t < best) {
       best = t;
       p.layout = c.layout;
@@ -336,19 +350,19 @@ Plan make_plan(int dtype, int N, int H, int V, int k, bool dma, bool vec) {
     p.BH = kb::FEW_ROWS;
     p.BV = few_cw;
   } else if (dma_path && dtype == KB_BF16) {
-    pick_by_model(kBf16DmaCosts, N, H, V, true, false, kc_of(k), p);
+    pick_by_model(kBf16DmaCosts, N, H, V, true, false, k, p);
   } else if (direct) {
     if (dtype == KB_F32)
-      pick_by_model(kF32DirectCosts, N, H, V, false, false, kc_of(k), p);
+      pick_by_model(kF32DirectCosts, N, H, V, false, false, k, p);
     else
-      pick_by_model(kBf16DirectCosts, N, H, V, false, false, kc_of(k), p);
+      pick_by_model(kBf16DirectCosts, N, H, V, false, false, k, p);
   } else if (dtype == KB_F32) {
     if (dma_path)
-      pick_by_model(kF32DmaCosts, N, H, V, true, true, kc_of(k), p);
+      pick_by_model(kF32DmaCosts, N, H, V, true, true, k, p);
     else
-      pick_by_model(kF32Costs, N, H, V, false, true, kc_of(k), p);
+      pick_by_model(kF32Costs, N, H, V, false, true, k, p);
   } else {
-    pick_by_model(kBf16Costs, N, H, V, false, true, kc_of(k), p);
+    pick_by_model(kBf16Costs, N, H, V, false, true, k, p);
   }
   if (p.layout != kb::K1_FEW)
     apply_tile_override(dma_path, dtype == KB_BF16 && dma_path && V >= kWideMinCols, direct,

@@ -229,9 +229,10 @@ def test_shard_argument_checks():
     # multiples of 8), 16-byte aligned bf16 operands -> 12 row tiles x 15 splits of 3 word tiles
     assert L.kb_shard_splits(1, 3072, 1024, 11256, 12, FAKE, FAKE, FAKE, ctypes.byref(n)) == KB_OK
     assert n.value == 15
-    # 11,250 words (V % 8 != 0) take the register-staged kernel's 128-word tiles: 18 splits of 5
+    # 11,250 words (V % 8 != 0) take the register-staged kernel, and its splits
+    plan = binding.kbest_plan(1, 3072, 1024, 11250, 12)
     assert L.kb_shard_splits(1, 3072, 1024, 11250, 12, FAKE, FAKE, FAKE, ctypes.byref(n)) == KB_OK
-    assert n.value == 18
+    assert n.value == plan["splits"] and plan["kernel"] == "reg"
     assert L.kb_shard_splits(1, 0, 1024, 11250, 12, None, None, None, ctypes.byref(n)) == KB_OK and n.value == 0
     assert L.kb_shard_splits(1, 3072, 1024, 11250, 12, FAKE, FAKE, FAKE, None) == KB_ERR_INVALID_ARG
     assert L.kb_shard_splits(1, 64, 1024, 8, 12, FAKE, FAKE, FAKE, ctypes.byref(n)) == KB_ERR_INVALID_ARG   # k > V

@@ -22,6 +22,13 @@ def _p(dt, N, H, V, aligned=True):
 
 
 def test_tile_override_follows_the_path(tile_env):
+    def ignored(tile, *step, **kw):
+        # the choice, and its splits, are those made without the override
+        tile_env(None)
+        want = kb.kbest_plan(*step, 5, **kw)
+        tile_env(tile)
+        return kb.kbest_plan(*step, 5, **kw) == want
+
     tile_env(None)
     assert _p(kb.KB_BF16, 640, 1024, 60000) == "wide 256x256"
     tile_env("32x512")
@@ -30,19 +37,47 @@ def test_tile_override_follows_the_path(tile_env):
     assert _p(kb.KB_F32, 640, 1000, 60000) == "reg 32x512"
     tile_env("256x256")
     assert _p(kb.KB_BF16, 40, 1024, 50000) == "wide 256x256"
-    assert _p(kb.KB_F32, 320, 512, 30000) == "dma 64x128"             # no 256 x 256 tile there: ignored
-    assert _p(kb.KB_F32, 320, 520, 30000) == "reg 32x256"
-    assert _p(kb.KB_BF16, 640, 1024, 60000, aligned=False) == "reg 256x128"
-    assert _p(kb.KB_BF16, 300, 128, 200) == "dma 32x128"              # V < 256: ignored
+    assert ignored("256x256", kb.KB_F32, 320, 512, 30000)             # no 256 x 256 tile there
+    assert ignored("256x256", kb.KB_F32, 320, 520, 30000)
+    assert ignored("256x256", kb.KB_BF16, 640, 1024, 60000, aligned=False)
+    assert ignored("256x256", kb.KB_BF16, 300, 128, 200)              # V < 256
     tile_env("64x128")
     assert _p(kb.KB_BF16, 640, 1024, 60000) == "dma 64x128"
     assert _p(kb.KB_F32, 640, 1024, 60000) == "dma 64x128"
-    assert _p(kb.KB_BF16, 640, 1000, 60000) == "reg 256x128"            # the register-staged path has no 64-row tile: ignored
+    assert ignored("64x128", kb.KB_BF16, 640, 1000, 60000)            # the register-staged path has no such tile
+    assert ignored("64x256", kb.KB_BF16, 640, 16, 60000)              # nor has the direct kernel this one
+    tile_env("32x512")
+    assert _p(kb.KB_BF16, 640, 16, 60000) == "reg 32x512"
     tile_env("128x256")
     assert _p(kb.KB_F32, 5, 256, 8000) == "few 8x64"                  # the few-row kernel keeps its steps
     for bad in ("64x64", "32x256x", "x", "", "256"):
         tile_env(bad)
         assert _p(kb.KB_BF16, 640, 1024, 60000) == "wide 256x256"
+
+
+def test_small_tiles_only_one_per_split():
+    # of several in turn they were slower than the model says; every path, row
+    # and word count still has a tile, the narrowest vocabularies included
+    for dt in (kb.KB_F32, kb.KB_BF16):
+        for H in (16, 256, 500, 1024):
+            for V in (1, 100, 130, 200, 3001, 30000, 50000, 90001):
+                for N in (9, 24, 64, 100, 257, 300, 320, 640, 2560, 9000):
+                    p = kb.kbest_plan(dt, N, H, V, 1)
+                    assert p["tile_rows"] in (32, 64, 128, 256) and p["row_tiles"] == -(-N // p["tile_rows"])
+                    if p["tile_words"] == 128 and p["tile_rows"] < 128:
+                        assert p["tiles_per_split"] == 1
+
+
+@pytest.mark.parametrize("dt,N,H,V,not_tile", [
+    # shapes where one tile had been preferred against the measured times
+    (kb.KB_F32, 320, 520, 30000, "32x256"), (kb.KB_F32, 160, 264, 60000, "32x256"),
+    (kb.KB_F32, 160, 520, 60000, "32x256"), (kb.KB_BF16, 640, 1000, 90001, "256x128"),
+    (kb.KB_BF16, 320, 1024, 50000, "64x128"), (kb.KB_BF16, 257, 1024, 50000, "64x128"),
+    (kb.KB_BF16, 320, 512, 90000, "64x128")])
+def test_choice_is_not_the_slow_tile(tile_env, dt, N, H, V, not_tile):
+    tile_env(None)
+    p = kb.kbest_plan(dt, N, H, V, 5)
+    assert f"{p['tile_rows']}x{p['tile_words']}" != not_tile
 
 
 def test_workspace_follows_the_override(tile_env):
