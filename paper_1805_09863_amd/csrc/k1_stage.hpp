@@ -360,10 +360,12 @@ void k1_stage(K1Args a) {
   bool nan = false;
 #pragma unroll
   for (int hb = 0; hb < WH; ++hb) nan |= epi.st_s[hb] != epi.st_s[hb];
-  if (nan) ep.flag[0] = 1;
+  // (a word of its own: a slower wave may still be at its last look at a
+  // round's flag, past the round's last barrier)
+  if (nan) ep.flag[2] = 1;
   lds_barrier();
-  const bool again = ep.flag[0] != 0;
-  lds_barrier();
+  const bool again = ep.flag[2] != 0;
+  lds_barrier();  // every wave has read it before the cell starts anew
   if (!again) {
     epi.finish(ep, a, h0, split);
   } else {
