@@ -101,9 +101,11 @@ MASKED = [("f32", 300, 128, 2048, "128x256"), ("f32", 40, 65, 2051, "32x128"), (
 
 @pytest.mark.parametrize("case", range(len(MASKED)))
 @pytest.mark.parametrize("at", ["first", "middle", "last"])
-def test_words_masked_through_the_weights(kb, case, at, monkeypatch):
-    # a state of constant 1 carries a mask: -inf in its row of W takes a word
-    # out (probability 0), and the other words' scores are theirs
+@pytest.mark.parametrize("mask", ["-inf", "lowest"])
+def test_words_masked_through_the_weights(kb, case, at, mask, monkeypatch):
+    # a state of constant 1 carries a mask: -inf or the type's lowest number in
+    # its row of W takes a word out (probability 0), and the other words' scores
+    # are theirs
     dt, N, H, V, tile = MASKED[case]
     _pin(monkeypatch, tile)
     h, W, b = _operands(dt, N, H, V)
@@ -112,7 +114,7 @@ def test_words_masked_through_the_weights(kb, case, at, monkeypatch):
     masked = np.zeros(V, bool)
     masked[1::3] = True
     masked[V - 1] = True
-    W[c, torch.from_numpy(masked)] = -float("inf")
+    W[c, torch.from_numpy(masked)] = -float("inf") if mask == "-inf" else torch.finfo(W.dtype).min
     k = 4
     prev = torch.zeros(N)
     off = torch.arange(0, N + 1, 2, dtype=torch.int32)
