@@ -118,9 +118,10 @@ constexpr int kGmaxSplits = 16;
 // The wide kernel's W source offsets assume at least one full 256-word tile.
 constexpr int kWideMinCols = 256;
 
-// Shapes the DMA pipeline accepts, pointer alignment aside: 64 bytes of an h
-// row per stage and whole 4-stage tiles (bf16 H % 128, float32 H % 64), W
-// rows of whole 16-byte chunks.
+// Aligned shapes, pointers aside.  bf16: what the DMA pipeline accepts, 64 bytes
+// of an h row per stage and whole 4-stage tiles (H % 128), W rows of whole
+// 16-byte chunks.  float32, which is staged through registers either way: those
+// whose tiles are modelled, and run two to a CU, by a table of their own.
 bool dma_shape(int dtype, int H, int V) {
   return dtype == KB_BF16 ? (H % 128 == 0 && V % 8 == 0) : (H % 64 == 0 && V % 4 == 0);
 }
