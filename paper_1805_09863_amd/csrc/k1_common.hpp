@@ -72,7 +72,7 @@ struct alignas(16) SmemEpi {
   uint32_t tgk[2][L::BH];   // shared-threshold keys read at the tile's first stage
   float thr[L::BH];         // row's local threshold: k-th best score so far, or the seed
   int cnt[L::BH];           // candidates of the row this round (may exceed PC: the rest waits)
-  int flag[4];              // "some lane has candidates left" of the current and the next round; [2]: k1_stage's vote
+  int flag[4];              // "some lane has candidates left" of this and the next round; [2]: k1_stage's vote
   uint64_t lst[L::BH][KC + 1];  // the row's best keys of the split so far, best first; 0: none
   union {
     uint64_t pool[L::BH][X::PC + 1];  // this round's candidates

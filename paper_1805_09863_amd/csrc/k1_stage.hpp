@@ -34,7 +34,8 @@
 // 3.1e-8 for four, 5.4e-8 (4.0e-7) for 16: no less precise from three states
 // on.  (A first piece cut off, not rounded, left out up to 2^-22: 3.4e-8, at
 // most 2.4e-7.)  An operand that rounds to infinity, within 2^-9 of FLT_MAX,
-// counts as infinite below.  Six bf16 products of 32 cycles replace eight float32 ones of 64.
+// counts as infinite below.  Six bf16 products of 32 cycles replace eight
+// float32 ones of 64.
 #pragma once
 
 #include <type_traits>
@@ -353,10 +354,12 @@ void k1_stage(K1Args a) {
 
   // An infinite operand (in float32 also one whose first piece is) leaves NaN
   // among these products where its own is an infinity or a number: its pieces
-  // are inf and inf - inf, and states and pieces of zero meet it.  A NaN stays in its row's sum, so a cell that ends with one is
-  // done again as the direct kernel does it (whose infinities are the
-  // operands' own).  Without the shared thresholds: those that this pass has
-  // published are its own words', whose scores may come out an ulp lower.
+  // are inf and inf - inf, and states and pieces of zero meet it.  A NaN stays
+  // in its row's sum, so a cell that ends with one is done again as the direct
+  // kernel does it, whose infinities are the operands' own.  Without the shared
+  // thresholds: those that this pass has published are its own words', whose
+  // scores may come out an ulp lower.  (Again tile by tile, inside the loop, it
+  // cost every step 300 to 660 spilled registers.)
   bool nan = false;
 #pragma unroll
   for (int hb = 0; hb < WH; ++hb) nan |= epi.st_s[hb] != epi.st_s[hb];
